@@ -57,14 +57,13 @@ struct BatchArgs {
   int32_t nitems;
 };
 
-// Built for at least six waves per SIMD: at the compiler's default the
-// kernel took 84 VGPRs (five waves); asked for six it fits in 72 with no
-// spill and runs at seven (256 jobs: 1.947 -> 1.895 ms). Eight spills.
+// Built for at least six waves per SIMD, which it fits in 77 VGPRs without a
+// spill (at the compiler's default it took five waves and 3% longer; eight
+// spill).
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))) void batch_kernel(
     const BatchArgs a) {
   __shared__ int s_item;
   __shared__ DepthRec s_rec[kPlaceMax];   // contributors of the current depth job
-  __shared__ OverDesc s_od[kOverStage];   // layers of the current over job
   const int tid = threadIdx.x;
   while (true) {
     if (tid == 0)
@@ -95,22 +94,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))
       }
       continue;
     }
-    // an over job's layer descriptors go to LDS when they fit
     const int on = uniform(J.n);
     const OverDesc* od = a.odesc + J.desc_off;
-    if (on <= kOverStage) {
-      stage_layers(od, on, s_od);
-      od = s_od;
-    }
+    const OverDesc mine = lane_layer(od, 0, on);
     for (int tile = uniform(I.tile0); tile < t1; ++tile) {
       const int ty = tile / J.tiles_x, tx = tile - ty * J.tiles_x;
       const int x0 = J.vx + tx * J.tile_w, y0 = J.vy + ty * J.tile_h;
       const int tw = min(J.tile_w, J.vx + J.vw - x0), th = min(J.tile_h, J.vy + J.vh - y0);
       if (J.fmt == CMP_RGBA32F) {
-        over_tile_seq<CMP_RGBA32F>(od, J.n, x0, y0, tw, th, (float*)J.out_color,
+        over_tile_seq<CMP_RGBA32F>(od, mine, on, x0, y0, tw, th, (float*)J.out_color,
                                    J.out_pitch, J.vx, J.vy, false);
       } else {
-        over_tile_seq<CMP_RGBA16F>(od, J.n, x0, y0, tw, th, (float*)J.out_color,
+        over_tile_seq<CMP_RGBA16F>(od, mine, on, x0, y0, tw, th, (float*)J.out_color,
                                    J.out_pitch, J.vx, J.vy, false);
       }
     }
@@ -292,7 +287,8 @@ extern "C" cmp_status cmp_batch_plan_create(const cmp_job* jobs, int32_t njobs,
     c.in = P->ins.back().data();
     c.order_b2f = j.kind == 1 ? P->orders.back().data() : nullptr;
     P->jobs.push_back(c);
-    const TileShape t = pick_tile(cache, j);
+    TileShape t = pick_tile(cache, j);
+    if (j.kind == 1) over_tile_shape(t.w, t.h);
     P->tiles.push_back(t);
     JobRec r;
     memset(&r, 0, sizeof r);

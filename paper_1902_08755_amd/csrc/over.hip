@@ -8,12 +8,11 @@
 namespace cmp {
 
 constexpr int kOverPerPass = 64;
-static_assert(kOverPerPass <= kOverStage, "a pass's layers are staged in LDS");
+static_assert(kOverPerPass <= kWave, "a pass's layers are held one per lane");
 
 struct OverArgs {
   OverDesc c[kOverPerPass];      // back to front
   Region reg[kMaxRegions];
-  uint8_t gb[kOverPerPass + 1];  // binary-swap group bounds (positions)
   float* out;
   int64_t out_pitch;
   int32_t vx, vy;
@@ -43,19 +42,16 @@ template <int FMT>
 __global__ __launch_bounds__(kThreads) void over_kernel(const OverArgs a) {
   int x0, y0, tw, th;
   region_tile(a.reg, a.nreg, a.tile_w, a.tile_h, x0, y0, tw, th);
-  __shared__ OverDesc s_d[kOverStage];
-  stage_layers(a.c, a.n, s_d);   // a.n <= kOverPerPass == kOverStage
-  over_tile_seq<FMT>(s_d, a.n, x0, y0, tw, th, a.out, a.out_pitch, a.vx, a.vy,
-                     a.accumulate != 0);
+  over_tile_seq<FMT>(a.c, lane_layer(a.c, 0, a.n), a.n, x0, y0, tw, th, a.out, a.out_pitch, a.vx,
+                     a.vy, a.accumulate != 0);
 }
 
 template <int FMT>
 __global__ __launch_bounds__(kThreads) void over_tree_kernel(const OverArgs a) {
   int x0, y0, tw, th;
   region_tile(a.reg, a.nreg, a.tile_w, a.tile_h, x0, y0, tw, th);
-  __shared__ OverDesc s_d[kOverStage];
-  stage_layers(a.c, a.n, s_d);
-  over_tile_tree<FMT>(s_d, a.gb, a.groups, x0, y0, tw, th, a.out, a.out_pitch, a.vx, a.vy);
+  extern __shared__ f32x4 lvl[];   // [log2(groups)][kThreads]
+  over_tile_tree<FMT>(a.c, a.n, a.groups, x0, y0, tw, th, a.out, a.out_pitch, a.vx, a.vy, lvl);
 }
 
 // ------------------------------------------------------------- backward
@@ -325,8 +321,9 @@ extern "C" cmp_status cmp_composite_over(const cmp_image* in, int32_t n, cmp_for
   if (rect_empty(viewport)) return CMP_OK;
   CMP_REQUIRE(out_rgba && ((uintptr_t)out_rgba & 15) == 0, "out_rgba must be 16-byte aligned");
   CMP_REQUIRE(out_pitch >= viewport.w, "out_pitch < viewport.w");
-  const int tw = tile.w ? tile.w : 64, th = tile.h ? tile.h : 4;
+  int tw = tile.w ? tile.w : 64, th = tile.h ? tile.h : 4;
   CMP_REQUIRE(tw > 0 && th > 0 && (int64_t)tw * th <= 65536, "bad tile %dx%d", tw, th);
+  over_tile_shape(tw, th);
   const bool tree = sched.kind == CMP_SCHED_BINARY_SWAP;
   if (tree && n > kOverPerPass) {
     set_error("binary-swap order supports at most %d layers", kOverPerPass);
@@ -350,10 +347,13 @@ extern "C" cmp_status cmp_composite_over(const cmp_image* in, int32_t n, cmp_for
   auto launch = [&]() -> cmp_status {
     const dim3 grid((unsigned)tiles), block(kThreads);
     if (a.groups > 0) {
+      int levels = 0;
+      while ((1 << levels) < a.groups) ++levels;
+      const unsigned lds = (unsigned)(levels * kThreads * sizeof(f32x4));
       if (fmt == CMP_RGBA32F)
-        hipLaunchKernelGGL(over_tree_kernel<CMP_RGBA32F>, grid, block, 0, s, a);
+        hipLaunchKernelGGL(over_tree_kernel<CMP_RGBA32F>, grid, block, lds, s, a);
       else
-        hipLaunchKernelGGL(over_tree_kernel<CMP_RGBA16F>, grid, block, 0, s, a);
+        hipLaunchKernelGGL(over_tree_kernel<CMP_RGBA16F>, grid, block, lds, s, a);
     } else {
       if (fmt == CMP_RGBA32F)
         hipLaunchKernelGGL(over_kernel<CMP_RGBA32F>, grid, block, 0, s, a);
@@ -370,7 +370,6 @@ extern "C" cmp_status cmp_composite_over(const cmp_image* in, int32_t n, cmp_for
       a.c[j] = OverDesc{I.color, I.pitch, I.roi.x, I.roi.y, rect_empty(I.roi) ? 0 : I.roi.w,
                         rect_empty(I.roi) ? 0 : I.roi.h};
     }
-    for (int g = 0; g <= P; ++g) a.gb[g] = (uint8_t)(((int64_t)g * n) / P);
     a.n = n;
     a.groups = P;
     return launch();
