@@ -6,24 +6,31 @@
 // Compression is a single pass over the input. A workgroup owns one block of
 // 4096 pixels of one image (16 consecutive pixels per lane) and encodes all
 // planes of it from registers:
+//   - the pixels become plane words by 4x4 byte transposes;
 //   - run starts: byte != previous byte, or a multiple of 256 pixels; the
-//     previous lane's last byte comes from a lane shuffle (a wave boundary is
-//     always a 256-pixel boundary);
+//     previous lane's last byte comes from the lane's DPP row of 16 (a row
+//     starts at a 256-pixel boundary);
 //   - token slots: a workgroup-wide exclusive scan of the per-lane run counts
-//     (eight 16-bit counters packed in two 64-bit words);
+//     (eight 16-bit counters packed in four 32-bit words);
 //   - run ends: the next start in the lane, else a suffix minimum of the first
 //     starts over the following lanes of the same 256-pixel segment;
 //   - the encoded block is staged in LDS, and its payload offset comes from a
 //     decoupled look-back over the blocks of the image (Merrill and Garland,
 //     "Single-pass Parallel Prefix Scan with Decoupled Look-back", 2016),
-//     one wave reading 64 predecessors' flags at a time.
-// The grid is at most one resident wave of workgroups. Workgroups draw
-// (image, block) slots from a ticket counter per image (each on its own
-// cache line), so the blocks of an image go out in order and only to
-// running workgroups: every block a look-back waits for is held by a
-// workgroup that makes progress, whatever else runs on the device. No
-// kernel clears the workspace: the last workgroup to finish zeroes the
-// tickets, and the look-back flags carry a per-call epoch.
+//     one wave reading 256 predecessors' flags at a time.
+// The grid is at most one resident wave of workgroups, which draw (image,
+// block) slots from a ticket counter per image (each on its own cache line),
+// so the blocks of an image go out in order and only to running workgroups:
+// every block a look-back waits for is held by a workgroup that makes
+// progress, whatever else runs on the device. No kernel clears the workspace:
+// the last workgroup to finish zeroes the tickets, and the look-back flags
+// carry a per-call epoch.
+// What bounds it: four blocks per compute unit (LDS and registers), each a
+// chain of about 3 to 4 us of pixel loads, 2 us of counting, 2 us of look-back,
+// 0.5 us of writes and 2 us of staging. Waits between blocks and contended
+// counters used to double that; see the order of work in the kernel, and
+// Drawer. 16 x 1920x1080 ROIs (107 MB): 58.3 -> 42.3 us; 8 x 3840x2160 (211
+// MB): 112 -> 63 us (3.3 TB/s).
 // Every workgroup derives the slot count from the device ROIs, so blocks that
 // the ROIs leave out cost nothing.
 //
@@ -45,25 +52,51 @@
 
 namespace cmp {
 
-// The tokens (run length - 1, value) of this lane's runs of one plane, from
-// token index idx on; 16-bit stores when the plane starts at an even offset.
+// The tokens (run length - 1, value) of this lane's runs of one plane, to
+// `dst` on: m (not 0) marks the runs' first pixels among the lane's 16, byte
+// j % 4 of w[j / 4] is pixel j, and the last run ends before pixel `after`
+// (counted from the lane's first). 16-bit stores when dst is even.
 template <bool kEven>
-__device__ __forceinline__ void emit_tokens(uint8_t* stage, uint32_t off, uint32_t idx, uint32_t m,
-                                            const uint32_t (&pw)[4], int q0, int next_after) {
-  while (m) {
-    const int j = __builtin_ctz(m);
+__device__ __forceinline__ void emit_tokens(uint8_t* dst, uint32_t m, const uint32_t (&w)[4],
+                                            uint32_t after) {
+  uint32_t j = (uint32_t)__builtin_ctz(m);
+  while (true) {
     m &= m - 1u;
-    const int end = m ? q0 + __builtin_ctz(m) : next_after;
-    const uint32_t w = j < 4 ? pw[0] : j < 8 ? pw[1] : j < 12 ? pw[2] : pw[3];
-    const uint32_t tokv = (uint32_t)(end - q0 - j - 1) | (((w >> (8 * (j & 3))) & 0xFFu) << 8);
+    const uint32_t next = m ? (uint32_t)__builtin_ctz(m) : after;
+    // byte j of the 16 as byte 1 of the token: from either half by v_perm
+    // (selector 0x0c gives a zero byte)
+    const uint32_t sel = ((j & 7u) << 8) | 0x0C0C000Cu;
+    const uint32_t lo = __builtin_amdgcn_perm(w[1], w[0], sel);
+    const uint32_t hi = __builtin_amdgcn_perm(w[3], w[2], sel);
+    const uint32_t tok = (j & 8u ? hi : lo) + next + ~j;   // | next - j - 1
     if (kEven) {
-      *reinterpret_cast<uint16_t*>(stage + off + 2 * idx) = (uint16_t)tokv;
+      *reinterpret_cast<uint16_t*>(dst) = (uint16_t)tok;
     } else {
-      stage[off + 2 * idx] = (uint8_t)tokv;
-      stage[off + 2 * idx + 1] = (uint8_t)(tokv >> 8);
+      dst[0] = (uint8_t)tok;
+      dst[1] = (uint8_t)(tok >> 8);
     }
-    ++idx;
+    if (!m) break;
+    dst += 2;
+    j = next;
   }
+}
+
+// Bit j of the result: byte j % 4 of word j / 4 differs from the byte before
+// it (prev: the word whose last byte precedes the first). v_lerp_u8 with
+// 0xFF sets a byte's top bit exactly when the byte is not 0, and v_dot4 sums
+// the top bits with the weights of their positions.
+__device__ __forceinline__ uint32_t change_mask(const uint32_t (&w)[4], uint32_t prev) {
+  uint32_t t[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t x = w[i] ^ __builtin_amdgcn_alignbyte(w[i], i ? w[i - 1] : prev, 3);
+    t[i] = __builtin_amdgcn_lerp(x, 0xFFFFFFFFu, 0u) & 0x80808080u;
+  }
+  const uint32_t lo = __builtin_amdgcn_udot4(t[1], 0x80402010u,
+                                             __builtin_amdgcn_udot4(t[0], 0x08040201u, 0u, false), false);
+  const uint32_t hi = __builtin_amdgcn_udot4(t[3], 0x80402010u,
+                                             __builtin_amdgcn_udot4(t[2], 0x08040201u, 0u, false), false);
+  return (lo + (hi << 8)) >> 7;
 }
 
 // kSwizzle: the colour words are bit-swizzled before their planes are taken
@@ -80,128 +113,92 @@ __global__ __launch_bounds__(kThreads, 4) void rle_compress_kernel(const RleCArg
   // slot, whose workgroup writes the header-only stream). Wave 0 computes the
   // table (lane i: image i, n <= 64; one load) into LDS.
   __shared__ int4 t_roi[kRleMax];
-  __shared__ uint32_t t_slots[kRleMax];
+  __shared__ uint32_t t_slots[kRleMax], t_first[kRleMax + 1];
   __shared__ int2 s_next;   // the slot drawn for the next iteration
-  slot_table(a, t_roi, t_slots);
+  slot_table(a, t_roi, t_slots, t_first);
   const uint32_t ep = call_epoch(a);
   __syncthreads();
 
-  // Slots come from per-image tickets (draw_slot), drawn by wave 1: the
-  // next slot's ticket is drawn once the current block's size is published,
-  // and its pixels are loaded while the current block finishes (look-back
-  // and writes). Drawing late keeps a ticket from waiting behind a whole
-  // block of encoding, which its successors would wait for too (measured:
-  // drawn at the start of the current block instead, 16 x 1920x1080 took
-  // 63.6 us; drawn here, 59.5 us). Holding a drawn slot while finishing the
-  // current one cannot deadlock: a block only waits for blocks whose tickets
-  // were drawn earlier, so every chain of waits ends at a workgroup that
-  // makes progress.
-  int img = (int)(blockIdx.x % (uint32_t)a.n);   // wave 1's current image
+  // Slots come from per-image tickets, drawn by wave 1: the first here, each
+  // further one while the block before it is staged.
+  Drawer drawer = draw_start(t_first, a.n);
   if (threadIdx.x / kWave == 1) {
-    const int2 sb = draw_slot(draw_ticket(a.tickets, img), a.tickets, t_slots, a.n, img);
+    const uint32_t t = draw_ticket(drawer, a.tickets, t_slots, a.n, -1);
+    const int2 sb = draw_slot(drawer, t, t_slots);
     if (threadIdx.x == kWave) s_next = sb;
   }
   __syncthreads();
   int2 cur = s_next;
-  if (cur.x < 0) {   // uniform: nothing left for this workgroup
-    finish_call(a, ep);
-    return;
-  }
-  uint32_t col[kPxPerLane], dep[kPxPerLane];
-  CSlot nx = compress_slot(cur, t_roi);
-  compress_load(a, nx, threadIdx.x, col, dep);
+  Pending pend{nullptr, nullptr, 0, 0, 0, 0, 0};
+  // An iteration loads and counts one block, publishes its size, then finds
+  // the offset of the block before it (staged in LDS), writes that one, and
+  // stages the new one. A block's size is thus published before the workgroup
+  // waits for anything: a wait for predecessors never delays a size that
+  // others wait for, so waits do not pile up along an image, and by the time
+  // a block looks back its predecessors have had a whole block's time to
+  // publish. (With the look-back ahead of the next block's loads, waits of 4
+  // to 9 us per block made up most of the kernel.) It also means that a wait
+  // cannot deadlock: between a slot's draw and its size there is none.
   while (true) {
-  // an opaque copy of the thread index: keeps per-lane values from being
-  // hoisted out of the loop and held in registers across iterations
-  int tid = threadIdx.x;
-  __asm__ volatile("" : "+v"(tid));
-  const int lane = tid % kWave;
-  const CSlot c = nx;
-  const int s = c.s, b = c.b, rx = c.rx, ry = c.ry, rw = c.rw, rh = c.rh;
-  // the next slot: its ticket is drawn after the scan, the draw is
-  // completed (and written to s_next) after the staging, before a barrier
-  const bool drawer = tid / kWave == 1;
-  uint32_t t_next = 0u;
-  auto finish_draw = [&]() {
-    if (drawer) {
-      const int2 sb = draw_slot(t_next, a.tickets, t_slots, a.n, img);
-      if (lane == 0) s_next = sb;
-    }
-  };
-  bool more = false;
-  {
-    const RleCImg I = a.im[s];
-    const int np = I.depth ? 8 : 4;
-    const int64_t npx = (int64_t)rw * rh;
-    const uint64_t nb = rle_nblocks(npx);
-    const uint64_t P0 = rle_p0(nb, np);
-    uint8_t* out = I.out;
-    if (nb == 0) {
-      if (drawer) t_next = draw_ticket(a.tickets, img);
-      finish_draw();
-      __syncthreads();   // s_next is written
-      cur = s_next;
-      more = cur.x >= 0;
-      if (more) {
-        nx = compress_slot(cur, t_roi);
-        compress_load(a, nx, tid, col, dep);
-      }
-      if (tid < 8) {
-        const uint32_t hdr[8] = {kRleMagic, (uint32_t)rx, (uint32_t)ry, 0u, 0u,
-                                 (uint32_t)np | (kSwizzle ? 0x100u : 0u), (uint32_t)kBlock, 0u};
-        reinterpret_cast<uint32_t*>(out)[tid] = hdr[tid];
-      }
-      if (tid == 0) a.out_size[s] = 32;
-    } else {
-      const int len = (int)imin64(kBlock, npx - (int64_t)b * kBlock);
-      const int q0 = tid * kPxPerLane;   // block-relative first pixel
-      if (kSwizzle) {
+    // an opaque copy of the thread index: keeps per-lane values from being
+    // hoisted out of the loop and held in registers across iterations
+    int tid = threadIdx.x;
+    __asm__ volatile("" : "+v"(tid));
+    const int lane = tid % kWave, wave = uniform(tid / kWave);
+    const bool have = uniform(cur.x) >= 0;
+    const int q0 = tid * kPxPerLane;   // block-relative first pixel
+    LookBack lb;
+    Pending now{nullptr, nullptr, 0, 0, 0, 0, 0};
+    uint32_t pl[8][4];   // plane words: byte j of pl[k][i] is plane k of pixel 4 i + j
+    uint32_t masks[8], ex[4], poff[8], total = 0, raw = 0;
+    int np = 0, len = 0;
+    if (have) {
+      const CSlot c = compress_slot(cur, t_roi);
+      const RleCImg I = a.im[c.s];
+      np = I.depth ? 8 : 4;
+      const int64_t npx = (int64_t)c.rw * c.rh;
+      const uint64_t nb = rle_nblocks(npx);   // 0: an empty ROI, a block without pixels
+      const uint64_t P0 = rle_p0(nb, np);
+      len = (int)imin64(kBlock, npx - (int64_t)c.b * kBlock);
+      {
+        PxLoad px;
+        compress_load(a, c, tid, px);
+        uint32_t col[kPxPerLane], dep[kPxPerLane];
+        compress_join(px, col, dep);
+        if (kSwizzle) {
 #pragma unroll
-        for (int j = 0; j < kPxPerLane; ++j) col[j] = swizzle_bits(col[j]);
-      }
-      const uint32_t pcol = __shfl_up(col[kPxPerLane - 1], 1);
-      const uint32_t pdep = __shfl_up(dep[kPxPerLane - 1], 1);
-      // plane words, made when needed: byte j of pw[j / 4] is plane k of pixel j
-      auto plane_words = [&](int k, uint32_t (&pw)[4]) {
-        const uint32_t* w = k < 4 ? col : dep;
+          for (int j = 0; j < kPxPerLane; ++j) col[j] = swizzle_bits(col[j]);
+        }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          pw[i] = gather_byte(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3], k & 3);
-      };
+        for (int i = 0; i < 4; ++i) {
+          transpose4x4(col[4 * i], col[4 * i + 1], col[4 * i + 2], col[4 * i + 3], pl[0][i],
+                       pl[1][i], pl[2][i], pl[3][i]);
+          transpose4x4(dep[4 * i], dep[4 * i + 1], dep[4 * i + 2], dep[4 * i + 3], pl[4][i],
+                       pl[5][i], pl[6][i], pl[7][i]);
+        }
+      }
+      // the flags that the pending block waits for are on their way meanwhile
+      if (pend.out && wave == 0) lookback_begin(lb, pend.flags, pend.b);
+
+      // ---- run starts (byte != previous byte, or a segment start: the first
+      // lane of a DPP row, so the previous lane's last byte comes from the
+      // row) as one 16-bit mask per plane, and their counts
       const bool seg_start = (tid % (kSeg / kPxPerLane)) == 0;
       const int nvalid = min(kPxPerLane, max(0, len - q0));
       const uint32_t vmask = (1u << nvalid) - 1u;
-
-      // ---- run starts (byte != previous byte, or a segment start) and counts:
-      // per pixel, which bytes differ from the previous pixel's (a nibble),
-      // then the 16 nibbles transposed into one 16-bit mask per plane
-      uint32_t nc_lo = 0, nc_hi = 0, nd_lo = 0, nd_hi = 0;
-#pragma unroll
-      for (int j = 0; j < kPxPerLane; ++j) {
-        const uint32_t c = nonzero_bytes(col[j] ^ (j ? col[j - 1] : pcol));
-        const uint32_t d = nonzero_bytes(dep[j] ^ (j ? dep[j - 1] : pdep));
-        if (j < 8) { nc_lo |= c << (4 * j); nd_lo |= d << (4 * j); }
-        else { nc_hi |= c << (4 * (j - 8)); nd_hi |= d << (4 * (j - 8)); }
-      }
-      uint32_t masks[8];
-      uint32_t cnt[4] = {0, 0, 0, 0};
+      uint32_t cnt[4] = {0, 0, 0, 0}, tot[4];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         masks[k] = 0;
         if (k >= np) continue;
-        uint32_t m = k < 4 ? nibble_bits(nc_lo, nc_hi, k) : nibble_bits(nd_lo, nd_hi, k - 4);
-        if (seg_start) m |= 1u;
-        m &= vmask;
-        masks[k] = m;
-        cnt[k >> 1] |= (uint32_t)__builtin_popcount(m) << (16 * (k & 1));
+        const uint32_t m = change_mask(pl[k], row_shr<1>(pl[k][3])) | (seg_start ? 1u : 0u);
+        masks[k] = m & vmask;
+        cnt[k >> 1] |= (uint32_t)__builtin_popcount(masks[k]) << (16 * (k & 1));
       }
-      uint32_t ex[4], tot[4];
-      block_scan32<4>(cnt, ex, tot, sh);
-      if (drawer) t_next = draw_ticket(a.tickets, img);
+      block_scan32_once<4>(cnt, ex, tot, sh);
 
       // ---- plane sizes and offsets (uniform)
-      uint32_t size[8], poff[8];
-      uint32_t total = 0;
+      uint32_t size[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         size[k] = 0;
@@ -209,117 +206,101 @@ __global__ __launch_bounds__(kThreads, 4) void rle_compress_kernel(const RleCArg
         if (k >= np) continue;
         const uint32_t ntok = (tot[k >> 1] >> (16 * (k & 1))) & 0xFFFFu;
         size[k] = (2 * ntok < (uint32_t)len) ? 2 * ntok : (uint32_t)len;
+        if (size[k] == (uint32_t)len) raw |= 1u << k;
         total += size[k];
       }
       const uint32_t padded = (uint32_t)align16(total);
-      // the block's size is known: publish it now (block 0: as the inclusive
-      // prefix), so that successors need not wait for the staging below
       uint64_t* flags = a.flags + I.flag_base;
+      // the block's size (block 0: as the inclusive prefix)
       if (tid == 0)
-        __hip_atomic_store(&flags[b], mkflag(b == 0 ? kIncl : kAgg, padded, ep), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&flags[c.b], mkflag(c.b == 0 ? kIncl : kAgg, padded, ep),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      now = Pending{I.out, flags, P0, nb, c.s, c.b, padded};
 
-      // ---- stage the encoded block in LDS
-      const int seg_end = min(len, ((q0 / kSeg) + 1) * kSeg);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        if (k >= np) continue;
-        const uint32_t m = masks[k];
-        const uint32_t off = poff[k];
-        uint32_t pw[4];
-        plane_words(k, pw);
-        if (size[k] != (uint32_t)len) {
-          // a run ends at the next start: in this lane, else the first start
-          // of the following lanes of the segment (a suffix minimum over the
-          // lane's DPP row), else the segment end
-          int fs = m ? q0 + __builtin_ctz(m) : seg_end;
-          fs = min(fs, row_shl_fill<1>(fs, seg_end));
-          fs = min(fs, row_shl_fill<2>(fs, seg_end));
-          fs = min(fs, row_shl_fill<4>(fs, seg_end));
-          fs = min(fs, row_shl_fill<8>(fs, seg_end));
-          const int next_after = row_shl_fill<1>(fs, seg_end);
-          const uint32_t tok0 = (ex[k >> 1] >> (16 * (k & 1))) & 0xFFFFu;
-          if ((off & 1u) == 0)
-            emit_tokens<true>(stage, off, tok0, m, pw, q0, next_after);
-          else
-            emit_tokens<false>(stage, off, tok0, m, pw, q0, next_after);
-        } else if ((off & 3u) == 0 && q0 + kPxPerLane <= len) {
-          // raw plane, 4-byte aligned: four 32-bit stores per lane
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            *reinterpret_cast<uint32_t*>(stage + off + q0 + 4 * i) = pw[i];
-        } else {
-#pragma unroll
-          for (int j = 0; j < kPxPerLane; ++j)
-            if (q0 + j < len) stage[off + q0 + j] = (uint8_t)(pw[j >> 2] >> (8 * (j & 3)));
-        }
-      }
-      if (tid < (int)(padded - total)) stage[total + tid] = 0;
-      finish_draw();
-      __syncthreads();   // s_next is written
-      cur = s_next;
-      more = cur.x >= 0;
-
-      // ---- decoupled look-back for the payload offset: wave 0 reads the
-      // flags of 256 predecessors at once (4 per lane, each load instruction
-      // contiguous over the lanes), sums the aggregates up to the nearest
-      // inclusive prefix, and moves the window back if it has none
-      bool lb_poison = false;
-      uint32_t lb_excl = 0;
-      if (tid < kWave) {
-        lb_excl = lookback_excl(flags, b, padded, a.wait_limit, ep, lb_poison);
-        if (lane == 0) {
-          s_excl = lb_excl;
-          s_poison = lb_poison ? 1 : 0;
-          if (lb_poison) a.status[s] = CMP_ETIMEOUT;
-        }
-      }
-      // the next slot's pixels go in flight: waves 1..3 during the look-back,
-      // wave 0 after it (its flag loads must not wait behind these loads),
-      // then wave 0 publishes the block's inclusive prefix
-      if (more) {
-        nx = compress_slot(cur, t_roi);
-        compress_load(a, nx, tid, col, dep);
-      }
-      if (tid < kWave) publish_incl(flags, b, lb_excl, padded, lb_poison, ep);
-      __syncthreads();
-      const uint32_t excl = s_excl;
-      const bool poisoned = s_poison != 0;
-
-      // ---- tables, header, payload
-      uint32_t* tbl = reinterpret_cast<uint32_t*>(out + 32);
-      if (tid < np) {
+      // ---- header and the block's plane sizes
+      uint32_t* tbl = reinterpret_cast<uint32_t*>(I.out + 32);
+      if (nb != 0 && tid < np) {
         uint32_t v = 0;
 #pragma unroll
         for (int k = 0; k < 8; ++k)
           if (k == tid) v = size[k];
-        tbl[nb + (uint64_t)b * np + tid] = v;
+        tbl[nb + (uint64_t)c.b * np + tid] = v;
       }
-      // a poisoned block's offset is unknown: its table entry is made invalid
-      // (not a multiple of 16, which decompression rejects) and its payload
-      // is not written
-      if (tid == 0) tbl[b] = poisoned ? 0xFFFFFFFFu : excl;
-      if (b == 0) {
+      if (c.b == 0) {
         if (tid < 8) {
-          const uint32_t hdr[8] = {kRleMagic, (uint32_t)rx, (uint32_t)ry, (uint32_t)rw,
-                                   (uint32_t)rh, (uint32_t)np | (kSwizzle ? 0x100u : 0u),
+          const uint32_t hdr[8] = {kRleMagic, (uint32_t)c.rx, (uint32_t)c.ry, (uint32_t)c.rw,
+                                   (uint32_t)c.rh, (uint32_t)np | (kSwizzle ? 0x100u : 0u),
                                    (uint32_t)kBlock, (uint32_t)nb};
-          reinterpret_cast<uint32_t*>(out)[tid] = hdr[tid];
+          reinterpret_cast<uint32_t*>(I.out)[tid] = hdr[tid];
         }
         const uint64_t tend = 32 + 4 * nb * (1 + (uint64_t)np);
-        if ((uint64_t)tid < P0 - tend) out[tend + tid] = 0;
+        if ((uint64_t)tid < P0 - tend) I.out[tend + tid] = 0;
       }
-      if ((uint64_t)b == nb - 1 && tid == 0) a.out_size[s] = poisoned ? 0 : P0 + excl + padded;
-      if (!poisoned) {
-        u32x4* dst = reinterpret_cast<u32x4*>(out + P0 + excl);
-        const u32x4* src = reinterpret_cast<const u32x4*>(stage);
-        for (uint32_t i = tid; i < padded / 16; i += kThreads)
-          __builtin_nontemporal_store(src[i], &dst[i]);   // streamed out, not re-read
+    } else if (pend.out && wave == 0) {
+      lookback_begin(lb, pend.flags, pend.b);
+    }
+
+    // ---- the pending block: its offset, its table entry, its payload
+    if (pend.out) write_pending(a, pend, lb, wave, lane, tid, ep, &s_excl, &s_poison, stage);
+    if (!have) break;
+    __syncthreads();   // the stage is read
+    uint32_t t_next = ~0u;
+    if (wave == 1) t_next = draw_ticket(drawer, a.tickets, t_slots, a.n, now.b);
+
+    // ---- stage the encoded block in LDS
+    const uint32_t seg_end = (uint32_t)min(len, ((q0 / kSeg) + 1) * kSeg);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (k >= np) continue;
+      const uint32_t m = masks[k];
+      const uint32_t off = poff[k];
+      if (!((raw >> k) & 1u)) {
+        // a run ends at the next start: in this lane, else the first start
+        // of the following lanes of the segment (a suffix minimum over the
+        // lane's DPP row), else the segment end
+        uint32_t fs = m ? (uint32_t)(q0 + __builtin_ctz(m)) : ~0u;
+        fs = min(fs, (uint32_t)row_shl_fill<1>((int)fs, -1));
+        fs = min(fs, (uint32_t)row_shl_fill<2>((int)fs, -1));
+        fs = min(fs, (uint32_t)row_shl_fill<4>((int)fs, -1));
+        fs = min(fs, (uint32_t)row_shl_fill<8>((int)fs, -1));
+        const uint32_t after = min((uint32_t)row_shl_fill<1>((int)fs, -1), seg_end) - (uint32_t)q0;
+        const uint32_t tok0 = (ex[k >> 1] >> (16 * (k & 1))) & 0xFFFFu;
+        if (m) {
+          if ((off & 1u) == 0)
+            emit_tokens<true>(stage + off + 2 * tok0, m, pl[k], after);
+          else
+            emit_tokens<false>(stage + off + 2 * tok0, m, pl[k], after);
+        }
+      } else if ((off & 1u) == 0 && q0 + kPxPerLane <= len) {
+        // raw plane at an even offset: 32-bit stores, shifted by a half word
+        // when the offset is 2 modulo 4 (the size of a run-coded plane before
+        // it is even)
+        uint8_t* dst = stage + off + q0;
+        if ((off & 2u) == 0) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) reinterpret_cast<uint32_t*>(dst)[i] = pl[k][i];
+        } else {
+          *reinterpret_cast<uint16_t*>(dst) = (uint16_t)pl[k][0];
+#pragma unroll
+          for (int i = 0; i < 3; ++i)
+            reinterpret_cast<uint32_t*>(dst + 2)[i] =
+                __builtin_amdgcn_alignbyte(pl[k][i + 1], pl[k][i], 2);
+          *reinterpret_cast<uint16_t*>(dst + 14) = (uint16_t)(pl[k][3] >> 16);
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < kPxPerLane; ++j)
+          if (q0 + j < len) stage[off + q0 + j] = (uint8_t)(pl[k][j >> 2] >> (8 * (j & 3)));
       }
     }
-  }
-  __syncthreads();   // the stage, the scan words and s_next are reused by the next slot
-  if (!more) break;
+    if ((uint32_t)tid < now.padded - total) stage[total + tid] = 0;
+    if (wave == 1) {
+      const int2 sb = draw_slot(drawer, t_next, t_slots);
+      if (lane == 0) s_next = sb;
+    }
+    pend = now;
+    __syncthreads();   // s_next is written
+    cur = s_next;
   }
   finish_call(a, ep);
 }

@@ -48,121 +48,123 @@ __device__ __forceinline__ uint32_t rl64_runs_of(uint32_t bytes) {
 }
 
 // ------------------------------------------------------------ compress
+// The order of work is the per-component compressor's: load, count and
+// publish a block, then look back for the block before it and write that one,
+// then stage the new one.
 __global__ __launch_bounds__(kThreads, 4) void rle64_compress_kernel(const RleCArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t stage[kStage];
   __shared__ uint32_t sh[16];
   __shared__ uint32_t s_excl;
   __shared__ int32_t s_poison;
   __shared__ int4 t_roi[kRleMax];
-  __shared__ uint32_t t_slots[kRleMax];
+  __shared__ uint32_t t_slots[kRleMax], t_first[kRleMax + 1];
   __shared__ int2 s_next;   // the slot drawn for the next iteration
-  slot_table(a, t_roi, t_slots);
+  slot_table(a, t_roi, t_slots, t_first);
   const uint32_t ep = call_epoch(a);
   __syncthreads();
-
-  // Slots as in the per-component compressor: per-image tickets drawn by
-  // wave 1, the next one after the current block's size is published.
-  int img = (int)(blockIdx.x % (uint32_t)a.n);
+  Drawer drawer = draw_start(t_first, a.n);
   if (threadIdx.x / kWave == 1) {
-    const int2 sb = draw_slot(draw_ticket(a.tickets, img), a.tickets, t_slots, a.n, img);
+    const uint32_t t = draw_ticket(drawer, a.tickets, t_slots, a.n, -1);
+    const int2 sb = draw_slot(drawer, t, t_slots);
     if (threadIdx.x == kWave) s_next = sb;
   }
   __syncthreads();
   int2 cur = s_next;
-  if (cur.x < 0) {   // uniform: nothing left for this workgroup
-    finish_call(a, ep);
-    return;
-  }
-  uint32_t col[kPxPerLane], dep[kPxPerLane];
-  CSlot nx = compress_slot(cur, t_roi);
-  compress_load(a, nx, threadIdx.x, col, dep);
+  Pending pend{nullptr, nullptr, 0, 0, 0, 0, 0};
   while (true) {
-  int tid = threadIdx.x;   // opaque per iteration (see the per-component compressor)
-  __asm__ volatile("" : "+v"(tid));
-  const int lane = tid % kWave;
-  const CSlot c = nx;
-  const int s = c.s, b = c.b, rx = c.rx, ry = c.ry, rw = c.rw, rh = c.rh;
-  const bool drawer = tid / kWave == 1;
-  uint32_t t_next = 0u;
-  auto finish_draw = [&]() {
-    if (drawer) {
-      const int2 sb = draw_slot(t_next, a.tickets, t_slots, a.n, img);
-      if (lane == 0) s_next = sb;
-    }
-  };
-  bool more = false;
-  const RleCImg I = a.im[s];
-  const int ns = I.depth ? 2 : 1;
-  const int64_t npx = (int64_t)rw * rh;
-  const uint64_t nb = rle_nblocks(npx);
-  const uint64_t P0 = rle_p0(nb, ns);
-  uint8_t* out = I.out;
-  if (nb == 0) {
-    if (drawer) t_next = draw_ticket(a.tickets, img);
-    finish_draw();
-    __syncthreads();   // s_next is written
-    cur = s_next;
-    more = cur.x >= 0;
-    if (more) {
-      nx = compress_slot(cur, t_roi);
-      compress_load(a, nx, tid, col, dep);
-    }
-    if (tid < 8) {
-      const uint32_t hdr[8] = {kRl64Magic, (uint32_t)rx, (uint32_t)ry, 0u, 0u, (uint32_t)ns,
-                               (uint32_t)kBlock, 0u};
-      reinterpret_cast<uint32_t*>(out)[tid] = hdr[tid];
-    }
-    if (tid == 0) a.out_size[s] = 32;
-  } else {
-    const int len = (int)imin64(kBlock, npx - (int64_t)b * kBlock);
-    const int m = (len + 1) / 2;   // symbols of the block (an odd last pixel pairs with 0)
-    const int j0 = tid * kSymLane;
-    const int nsv = min(kSymLane, max(0, m - j0));
-    const uint32_t vmask = (1u << nsv) - 1u;
-    const bool seg_start = (tid % (kSeg / kPxPerLane)) == 0;
-
-    // ---- run starts of the symbols (pixel 2i low, 2i + 1 high) per stream:
-    // symbol i differs from the one before it (the previous lane's last
-    // symbol for i = 0), or starts a segment
-    uint32_t mask[2] = {0u, 0u};
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      if (k >= ns) continue;
-      const uint32_t* w = k ? dep : col;
-      const uint32_t plo = __shfl_up(w[kPxPerLane - 2], 1), phi = __shfl_up(w[kPxPerLane - 1], 1);
-      uint32_t mm = 0;
-#pragma unroll
-      for (int i = 0; i < kSymLane; ++i) {
-        const uint32_t lo0 = i ? w[2 * i - 2] : plo, hi0 = i ? w[2 * i - 1] : phi;
-        if ((w[2 * i] ^ lo0) | (w[2 * i + 1] ^ hi0)) mm |= 1u << i;
+    int tid = threadIdx.x;   // opaque per iteration (see the per-component compressor)
+    __asm__ volatile("" : "+v"(tid));
+    const int lane = tid % kWave, wave = uniform(tid / kWave);
+    const bool have = uniform(cur.x) >= 0;
+    const int j0 = tid * kSymLane;   // block-relative first symbol
+    LookBack lb;
+    Pending now{nullptr, nullptr, 0, 0, 0, 0, 0};
+    uint32_t col[kPxPerLane], dep[kPxPerLane];
+    uint32_t mask[2] = {0u, 0u}, ex[1], runs[2], poff[2], total = 0, raw = 0;
+    int ns = 0, m = 0, nsv = 0;
+    if (have) {
+      const CSlot c = compress_slot(cur, t_roi);
+      const RleCImg I = a.im[c.s];
+      ns = I.depth ? 2 : 1;
+      const int64_t npx = (int64_t)c.rw * c.rh;
+      const uint64_t nb = rle_nblocks(npx);   // 0: an empty ROI, a block without pixels
+      const uint64_t P0 = rle_p0(nb, ns);
+      const int len = (int)imin64(kBlock, npx - (int64_t)c.b * kBlock);
+      m = (len + 1) / 2;   // symbols of the block (an odd last pixel pairs with 0)
+      nsv = min(kSymLane, max(0, m - j0));
+      {
+        PxLoad px;
+        compress_load(a, c, tid, px);
+        compress_join(px, col, dep);
       }
-      if (seg_start) mm |= 1u;
-      mask[k] = mm & vmask;
-    }
-    uint32_t cnt[1] = {(uint32_t)__builtin_popcount(mask[0]) |
-                       ((uint32_t)__builtin_popcount(mask[1]) << 16)};
-    uint32_t ex[1], tot[1];
-    block_scan32<1>(cnt, ex, tot, sh);
-    if (drawer) t_next = draw_ticket(a.tickets, img);
+      if (pend.out && wave == 0) lookback_begin(lb, pend.flags, pend.b);
 
-    // ---- stream sizes and offsets (uniform; multiples of 8)
-    uint32_t size[2], poff[2], runs[2];
-    uint32_t total = 0;
+      // ---- run starts of the symbols (pixel 2i low, 2i + 1 high) per stream:
+      // symbol i differs from the one before it (the previous lane's last
+      // symbol for i = 0), or starts a segment (the first lane of a DPP row)
+      const uint32_t vmask = (1u << nsv) - 1u;
+      const bool seg_start = (tid % (kSeg / kPxPerLane)) == 0;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      size[k] = 0;
-      poff[k] = total;
-      runs[k] = (tot[0] >> (16 * k)) & 0xFFFFu;
-      if (k >= ns) continue;
-      const uint32_t tb = rl64_token_bytes(runs[k]);
-      size[k] = tb < 8u * (uint32_t)m ? tb : 8u * (uint32_t)m;
-      total += size[k];
+      for (int k = 0; k < 2; ++k) {
+        if (k >= ns) continue;
+        const uint32_t* w = k ? dep : col;
+        const uint32_t plo = row_shr<1>(w[kPxPerLane - 2]), phi = row_shr<1>(w[kPxPerLane - 1]);
+        uint32_t mm = 0;
+#pragma unroll
+        for (int i = 0; i < kSymLane; ++i) {
+          const uint32_t lo = i ? w[2 * i - 2] : plo, hi = i ? w[2 * i - 1] : phi;
+          if (w[2 * i] != lo || w[2 * i + 1] != hi) mm |= 1u << i;
+        }
+        if (seg_start) mm |= 1u;
+        mask[k] = mm & vmask;
+      }
+      const uint32_t cnt[1] = {(uint32_t)__builtin_popcount(mask[0]) |
+                               ((uint32_t)__builtin_popcount(mask[1]) << 16)};
+      uint32_t tot[1];
+      block_scan32_once<1>(cnt, ex, tot, sh);
+
+      // ---- stream sizes and offsets (uniform)
+      uint32_t size[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        size[k] = 0;
+        poff[k] = total;
+        runs[k] = (tot[0] >> (16 * k)) & 0xFFFFu;
+        if (k >= ns) continue;
+        const uint32_t tb = rl64_token_bytes(runs[k]);
+        if (tb >= 8u * (uint32_t)m) raw |= 1u << k;
+        size[k] = min(tb, 8u * (uint32_t)m);
+        total += size[k];
+      }
+      const uint32_t padded = (uint32_t)align16(total);
+      uint64_t* flags = a.flags + I.flag_base;
+      if (tid == 0)
+        __hip_atomic_store(&flags[c.b], mkflag(c.b == 0 ? kIncl : kAgg, padded, ep),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      now = Pending{I.out, flags, P0, nb, c.s, c.b, padded};
+
+      // ---- header and the block's stream sizes
+      uint32_t* tbl = reinterpret_cast<uint32_t*>(I.out + 32);
+      if (nb != 0 && tid < ns) tbl[nb + (uint64_t)c.b * ns + tid] = tid ? size[1] : size[0];
+      if (c.b == 0) {
+        if (tid < 8) {
+          const uint32_t hdr[8] = {kRl64Magic, (uint32_t)c.rx, (uint32_t)c.ry, (uint32_t)c.rw,
+                                   (uint32_t)c.rh, (uint32_t)ns, (uint32_t)kBlock, (uint32_t)nb};
+          reinterpret_cast<uint32_t*>(I.out)[tid] = hdr[tid];
+        }
+        const uint64_t tend = 32 + 4 * nb * (1 + (uint64_t)ns);
+        if ((uint64_t)tid < P0 - tend) I.out[tend + tid] = 0;
+      }
+    } else if (pend.out && wave == 0) {
+      lookback_begin(lb, pend.flags, pend.b);
     }
-    const uint32_t padded = (uint32_t)align16(total);
-    uint64_t* flags = a.flags + I.flag_base;
-    if (tid == 0)
-      __hip_atomic_store(&flags[b], mkflag(b == 0 ? kIncl : kAgg, padded, ep), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
+
+    // ---- the pending block: its offset, its table entry, its payload
+    if (pend.out) write_pending(a, pend, lb, wave, lane, tid, ep, &s_excl, &s_poison, stage);
+    if (!have) break;
+    __syncthreads();   // the stage is read
+    uint32_t t_next = ~0u;
+    if (wave == 1) t_next = draw_ticket(drawer, a.tickets, t_slots, a.n, now.b);
 
     // ---- stage the encoded block in LDS
     const int seg_end = min(m, (j0 / kSymSeg + 1) * kSymSeg);
@@ -171,7 +173,7 @@ __global__ __launch_bounds__(kThreads, 4) void rle64_compress_kernel(const RleCA
       if (k >= ns) continue;
       const uint32_t* w = k ? dep : col;
       const uint32_t off = poff[k];
-      if (size[k] != 8u * (uint32_t)m) {
+      if (!((raw >> k) & 1u)) {
         // a run ends at the next start: in this lane, else the first start
         // of the following lanes of the segment, else the segment end
         uint32_t mm = mask[k];
@@ -205,55 +207,14 @@ __global__ __launch_bounds__(kThreads, 4) void rle64_compress_kernel(const RleCA
             *reinterpret_cast<uint2*>(stage + off + 8 * (j0 + i)) = uint2{w[2 * i], w[2 * i + 1]};
       }
     }
-    if (tid < (int)(padded - total)) stage[total + tid] = 0;
-    finish_draw();
+    if ((uint32_t)tid < now.padded - total) stage[total + tid] = 0;
+    if (wave == 1) {
+      const int2 sb = draw_slot(drawer, t_next, t_slots);
+      if (lane == 0) s_next = sb;
+    }
+    pend = now;
     __syncthreads();   // s_next is written
     cur = s_next;
-    more = cur.x >= 0;
-
-    // ---- payload offset (wave 0); the next slot's pixels go in flight
-    bool lb_poison = false;
-    uint32_t lb_excl = 0;
-    if (tid < kWave) {
-      lb_excl = lookback_excl(flags, b, padded, a.wait_limit, ep, lb_poison);
-      if (lane == 0) {
-        s_excl = lb_excl;
-        s_poison = lb_poison ? 1 : 0;
-        if (lb_poison) a.status[s] = CMP_ETIMEOUT;
-      }
-    }
-    if (more) {
-      nx = compress_slot(cur, t_roi);
-      compress_load(a, nx, tid, col, dep);
-    }
-    if (tid < kWave) publish_incl(flags, b, lb_excl, padded, lb_poison, ep);
-    __syncthreads();
-    const uint32_t excl = s_excl;
-    const bool poisoned = s_poison != 0;
-
-    // ---- tables, header, payload
-    uint32_t* tbl = reinterpret_cast<uint32_t*>(out + 32);
-    if (tid < ns) tbl[nb + (uint64_t)b * ns + tid] = tid ? size[1] : size[0];
-    if (tid == 0) tbl[b] = poisoned ? 0xFFFFFFFFu : excl;
-    if (b == 0) {
-      if (tid < 8) {
-        const uint32_t hdr[8] = {kRl64Magic, (uint32_t)rx, (uint32_t)ry, (uint32_t)rw,
-                                 (uint32_t)rh, (uint32_t)ns, (uint32_t)kBlock, (uint32_t)nb};
-        reinterpret_cast<uint32_t*>(out)[tid] = hdr[tid];
-      }
-      const uint64_t tend = 32 + 4 * nb * (1 + (uint64_t)ns);
-      if ((uint64_t)tid < P0 - tend) out[tend + tid] = 0;
-    }
-    if ((uint64_t)b == nb - 1 && tid == 0) a.out_size[s] = poisoned ? 0 : P0 + excl + padded;
-    if (!poisoned) {
-      u32x4* dst = reinterpret_cast<u32x4*>(out + P0 + excl);
-      const u32x4* src = reinterpret_cast<const u32x4*>(stage);
-      for (uint32_t i = tid; i < padded / 16; i += kThreads)
-        __builtin_nontemporal_store(src[i], &dst[i]);   // streamed out, not re-read
-    }
-  }
-  __syncthreads();   // the stage, the scan words and s_next are reused by the next slot
-  if (!more) break;
   }
   finish_call(a, ep);
 }
@@ -408,7 +369,8 @@ __global__ __launch_bounds__(kThreads) void rle64_decompress_kernel(const RleDAr
     }
   }
   uint32_t ex[2], tot[2];
-  block_scan32<2>(sums, ex, tot, sh);
+  block_scan32_once<2>(sums, ex, tot, sh);
+  __syncthreads();
 #pragma unroll
   for (int k = 0; k < 2; ++k)
     if (runs[k] && tot[k] != (uint32_t)m) bad = true;
