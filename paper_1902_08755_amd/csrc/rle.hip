@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kThreads, 4) void rle_compress_kernel(const RleCArg
   // further one while the block before it is staged.
   Drawer drawer = draw_start(t_first, a.n);
   if (threadIdx.x / kWave == 1) {
-    const uint32_t t = draw_ticket(drawer, a.tickets, t_slots, a.n, -1);
+    const uint32_t t = draw_ticket(drawer, a.tickets);
     const int2 sb = draw_slot(drawer, t, t_slots);
     if (threadIdx.x == kWave) s_next = sb;
   }
@@ -139,6 +139,8 @@ __global__ __launch_bounds__(kThreads, 4) void rle_compress_kernel(const RleCArg
   // publish. (With the look-back ahead of the next block's loads, waits of 4
   // to 9 us per block made up most of the kernel.) It also means that a wait
   // cannot deadlock: between a slot's draw and its size there is none.
+  LookBack lb;
+  bool looking = false;   // the pending block's look-back has begun
   while (true) {
     // an opaque copy of the thread index: keeps per-lane values from being
     // hoisted out of the loop and held in registers across iterations
@@ -147,7 +149,6 @@ __global__ __launch_bounds__(kThreads, 4) void rle_compress_kernel(const RleCArg
     const int lane = tid % kWave, wave = uniform(tid / kWave);
     const bool have = uniform(cur.x) >= 0;
     const int q0 = tid * kPxPerLane;   // block-relative first pixel
-    LookBack lb;
     Pending now{nullptr, nullptr, 0, 0, 0, 0, 0};
     uint32_t pl[8][4];   // plane words: byte j of pl[k][i] is plane k of pixel 4 i + j
     uint32_t masks[8], ex[4], poff[8], total = 0, raw = 0;
@@ -236,16 +237,22 @@ __global__ __launch_bounds__(kThreads, 4) void rle_compress_kernel(const RleCArg
         const uint64_t tend = 32 + 4 * nb * (1 + (uint64_t)np);
         if ((uint64_t)tid < P0 - tend) I.out[tend + tid] = 0;
       }
-    } else if (pend.out && wave == 0) {
+    } else if (pend.out && !looking && wave == 0) {
       lookback_begin(lb, pend.flags, pend.b);
     }
 
     // ---- the pending block: its offset, its table entry, its payload
-    if (pend.out) write_pending(a, pend, lb, wave, lane, tid, ep, &s_excl, &s_poison, stage);
+    if (pend.out) {
+      write_pending(a, pend, lb, wave, lane, tid, ep, &s_excl, &s_poison, stage);
+      __syncthreads();   // the stage is read
+    }
     if (!have) break;
-    __syncthreads();   // the stage is read
+    draw_advance(drawer, t_slots, a.n, now.b);
     uint32_t t_next = ~0u;
-    if (wave == 1) t_next = draw_ticket(drawer, a.tickets, t_slots, a.n, now.b);
+    if (wave == 1) t_next = draw_ticket(drawer, a.tickets);
+    // the workgroup's last block looks back while it is staged
+    looking = drawer.img < 0;
+    if (looking && wave == 0) lookback_begin(lb, now.flags, now.b);
 
     // ---- stage the encoded block in LDS
     const uint32_t seg_end = (uint32_t)min(len, ((q0 / kSeg) + 1) * kSeg);
@@ -294,13 +301,16 @@ __global__ __launch_bounds__(kThreads, 4) void rle_compress_kernel(const RleCArg
       }
     }
     if ((uint32_t)tid < now.padded - total) stage[total + tid] = 0;
-    if (wave == 1) {
-      const int2 sb = draw_slot(drawer, t_next, t_slots);
-      if (lane == 0) s_next = sb;
-    }
     pend = now;
-    __syncthreads();   // s_next is written
-    cur = s_next;
+    cur = int2{-1, 0};
+    if (!looking) {   // (after the last block, write_pending's barrier is the next one)
+      if (wave == 1) {
+        const int2 sb = draw_slot(drawer, t_next, t_slots);
+        if (lane == 0) s_next = sb;
+      }
+      __syncthreads();   // s_next is written
+      cur = s_next;
+    }
   }
   finish_call(a, ep);
 }

@@ -64,20 +64,21 @@ __global__ __launch_bounds__(kThreads, 4) void rle64_compress_kernel(const RleCA
   __syncthreads();
   Drawer drawer = draw_start(t_first, a.n);
   if (threadIdx.x / kWave == 1) {
-    const uint32_t t = draw_ticket(drawer, a.tickets, t_slots, a.n, -1);
+    const uint32_t t = draw_ticket(drawer, a.tickets);
     const int2 sb = draw_slot(drawer, t, t_slots);
     if (threadIdx.x == kWave) s_next = sb;
   }
   __syncthreads();
   int2 cur = s_next;
   Pending pend{nullptr, nullptr, 0, 0, 0, 0, 0};
+  LookBack lb;
+  bool looking = false;   // the pending block's look-back has begun
   while (true) {
     int tid = threadIdx.x;   // opaque per iteration (see the per-component compressor)
     __asm__ volatile("" : "+v"(tid));
     const int lane = tid % kWave, wave = uniform(tid / kWave);
     const bool have = uniform(cur.x) >= 0;
     const int j0 = tid * kSymLane;   // block-relative first symbol
-    LookBack lb;
     Pending now{nullptr, nullptr, 0, 0, 0, 0, 0};
     uint32_t col[kPxPerLane], dep[kPxPerLane];
     uint32_t mask[2] = {0u, 0u}, ex[1], runs[2], poff[2], total = 0, raw = 0;
@@ -155,16 +156,22 @@ __global__ __launch_bounds__(kThreads, 4) void rle64_compress_kernel(const RleCA
         const uint64_t tend = 32 + 4 * nb * (1 + (uint64_t)ns);
         if ((uint64_t)tid < P0 - tend) I.out[tend + tid] = 0;
       }
-    } else if (pend.out && wave == 0) {
+    } else if (pend.out && !looking && wave == 0) {
       lookback_begin(lb, pend.flags, pend.b);
     }
 
     // ---- the pending block: its offset, its table entry, its payload
-    if (pend.out) write_pending(a, pend, lb, wave, lane, tid, ep, &s_excl, &s_poison, stage);
+    if (pend.out) {
+      write_pending(a, pend, lb, wave, lane, tid, ep, &s_excl, &s_poison, stage);
+      __syncthreads();   // the stage is read
+    }
     if (!have) break;
-    __syncthreads();   // the stage is read
+    draw_advance(drawer, t_slots, a.n, now.b);
     uint32_t t_next = ~0u;
-    if (wave == 1) t_next = draw_ticket(drawer, a.tickets, t_slots, a.n, now.b);
+    if (wave == 1) t_next = draw_ticket(drawer, a.tickets);
+    // the workgroup's last block looks back while it is staged
+    looking = drawer.img < 0;
+    if (looking && wave == 0) lookback_begin(lb, now.flags, now.b);
 
     // ---- stage the encoded block in LDS
     const int seg_end = min(m, (j0 / kSymSeg + 1) * kSymSeg);
@@ -208,13 +215,16 @@ __global__ __launch_bounds__(kThreads, 4) void rle64_compress_kernel(const RleCA
       }
     }
     if ((uint32_t)tid < now.padded - total) stage[total + tid] = 0;
-    if (wave == 1) {
-      const int2 sb = draw_slot(drawer, t_next, t_slots);
-      if (lane == 0) s_next = sb;
-    }
     pend = now;
-    __syncthreads();   // s_next is written
-    cur = s_next;
+    cur = int2{-1, 0};
+    if (!looking) {   // (after the last block, write_pending's barrier is the next one)
+      if (wave == 1) {
+        const int2 sb = draw_slot(drawer, t_next, t_slots);
+        if (lane == 0) s_next = sb;
+      }
+      __syncthreads();   // s_next is written
+      cur = s_next;
+    }
   }
   finish_call(a, ep);
 }

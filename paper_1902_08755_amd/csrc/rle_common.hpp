@@ -329,13 +329,16 @@ __device__ __forceinline__ Drawer draw_start(const uint32_t* t_first, int n) {
   return Drawer{img, 1u + (uint32_t)__builtin_amdgcn_readlane((int)(hi - lo), img < 0 ? 0 : img)};
 }
 
-// Lane 0 draws a ticket of the current image (whose latency can pass while
-// the wave works), if there is one to draw after ticket `last` (-1: none
-// drawn yet); ~0 otherwise.
-__device__ __forceinline__ uint32_t draw_ticket(Drawer& d, uint32_t* tickets,
-                                                const uint32_t* t_slots, int n, int64_t last) {
-  if (d.img >= 0 && last >= 0 && last + d.g >= (int64_t)t_slots[d.img])
+// The holder of ticket `last` moves on if its image has no further ticket for
+// it. Uniform over the workgroup.
+__device__ __forceinline__ void draw_advance(Drawer& d, const uint32_t* t_slots, int n, int last) {
+  if ((uint64_t)last + d.g >= (uint64_t)(uint32_t)uniform((int)t_slots[d.img]))
     d = Drawer{d.img + (int)gridDim.x < n ? d.img + (int)gridDim.x : -1, 1u};
+}
+
+// Lane 0 draws a ticket of the current image, whose latency can pass while
+// the wave works (~0 if there is no image).
+__device__ __forceinline__ uint32_t draw_ticket(const Drawer& d, uint32_t* tickets) {
   uint32_t t = ~0u;
   if (d.img >= 0 && threadIdx.x % kWave == 0)
     t = __hip_atomic_fetch_add(&tickets[d.img * kTicketStride], 1u, __ATOMIC_RELAXED,
@@ -509,7 +512,13 @@ __device__ __forceinline__ void slot_table(const RleCArgs& a, int4* t_roi, uint3
     const uint32_t rest = min(gridDim.x, all) - min(min(gridDim.x, all), (uint32_t)a.n);
     t_roi[lane] = int4{lx, ly, lw, lh};
     t_slots[lane] = lslots;
-    t_first[lane + 1] = (uint32_t)(((uint64_t)incl * rest) / all);
+    // a workgroup per slot if there are enough; else in proportion by a rounded
+    // factor (a 64-bit division takes longer than the rest of the table):
+    // ascending, and all of them in the end
+    const uint32_t share = all <= gridDim.x
+                               ? incl - min(incl, (uint32_t)lane + 1u)
+                               : (uint32_t)((float)incl * ((float)rest / (float)all));
+    t_first[lane + 1] = lane >= a.n - 1 ? rest : min(share, rest);
     if (lane == 0) t_first[0] = 0;
   }
 }
