@@ -35,14 +35,25 @@
 // the ROIs leave out cost nothing.
 //
 // Decompression: a grid-stride loop over the blocks of all streams (counted
-// from the stream headers); per block: table checks (uniform loads, every
-// lane checks), payload to LDS, each lane's 16-byte window of every plane
-// (its 16 raw bytes or its 8 tokens), one workgroup scan of the run-length
-// sums of all run-coded planes, each run's value and start bit scattered
-// into LDS, and per lane a fill of its 16 pixels from the last run start.
-// The value entering a lane comes from a scan over its DPP row of 16 lanes:
-// a row covers one 256-pixel segment, which no run crosses. Pixels are
-// assembled in registers and written with 16-byte stores.
+// from the stream headers); per block: table checks (made uniform: scalar
+// work), each lane's 16-byte window of every plane straight from the stream
+// (its 16 raw bytes, its up to 8 tokens, or the token of its 256-pixel
+// segment), one workgroup scan of the run-length sums of the run-coded planes
+// with more than a run per segment, the runs of up to four of those planes at
+// a time scattered into LDS (value and start bit), and per lane a fill of its
+// 16 pixels from the last run start. The value entering a lane comes from a
+// scan over its DPP row of 16 lanes: a row covers one 256-pixel segment,
+// which no run crosses. Pixels are assembled in registers, restaged through
+// the wave's part of LDS and written with 16-byte stores, colour, then depth.
+// What bounds it: the memory system (8 x 3840x2160 ROIs, 52 MB read and 160
+// MB written: 53 us, 4.0 TB/s, where a copy reaches 5.0) and, where there are
+// only about two blocks per workgroup, the two dependent round trips (table,
+// windows; 2.3 us each among the stores) that each block starts with. At 62 us
+// it had four workgroups per compute unit (40 KB of LDS for eight planes of
+// values), 1350 vector instructions per block and wave (now 900) and its row
+// ends stored through a division each. Six workgroups (80 registers, one
+// spilled): 58 us; the next block's windows prefetched into registers at four:
+// 53 us, and slower for one large image (25 against 22 us).
 #include <string.h>
 
 #include <atomic>
@@ -316,41 +327,6 @@ __global__ __launch_bounds__(kThreads, 4) void rle_compress_kernel(const RleCArg
 }
 
 // ---------------------------------------------------------- decompress
-// Run-length sums of a block's planes, 21-bit fields, three per word: a
-// plane of < 2048 tokens of <= 256 pixels sums to < 2^21, so no field can
-// overflow into the next, whatever the stream holds.
-__device__ __forceinline__ int fld_word(int k) { return k / 3; }
-__device__ __forceinline__ int fld_shift(int k) { return 21 * (k % 3); }
-constexpr uint64_t kFld = (1u << 21) - 1;
-
-
-// Exclusive workgroup scan with a single barrier: the caller keeps a barrier
-// between these reads of `sh` and its next writes.
-template <int kW>
-__device__ __forceinline__ void block_scan_once(const uint64_t (&v)[kW], uint64_t (&ex)[kW],
-                                                uint64_t (&tot)[kW], uint64_t* sh) {
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  uint64_t inc[kW];
-#pragma unroll
-  for (int i = 0; i < kW; ++i) {
-    inc[i] = wave_incl_scan(v[i]);
-    if (lane == kWave - 1) sh[4 * i + wave] = inc[i];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < kW; ++i) {
-    uint64_t p = 0, t = 0;
-#pragma unroll
-    for (int w = 0; w < kThreads / kWave; ++w) {
-      const uint64_t x = sh[4 * i + w];
-      if (w < wave) p += x;
-      t += x;
-    }
-    ex[i] = p + inc[i] - v[i];
-    tot[i] = t;
-  }
-}
-
 // 16 bytes at any byte offset `off` of a buffer whose first `end` bytes
 // (end >= 16) may be read: load16_from reads them with one 16-byte load from
 // src = min(off, end - 16); when the bytes run past `end`, load16_fix shifts
@@ -373,11 +349,41 @@ __device__ __forceinline__ u32x4 load16_fix(u32x4 v, uint32_t src, uint32_t off)
   return v;
 }
 
-__global__ __launch_bounds__(kThreads, 4) void rle_decompress_kernel(const RleDArgs a) {
+// A block to decode: what its table entries say. All uniform.
+struct DBlock {
+  int np, len;
+  uint32_t pay, btotal;
+  uint32_t tokmask;   // planes stored as runs
+  uint32_t segmask;   // ... of one run per 256-pixel segment
+  uint32_t size[8], poff[8];
+  // Tokens per lane of a run-coded plane: T tokens are taken ceil(T / 256) to
+  // a lane (at most 8), so that all four waves share the scatter.
+  __device__ __forceinline__ int tpl(int k) const {
+    return max(1, ((int)(size[k] / 2) + kThreads - 1) / kThreads);
+  }
+  // This lane's tokens.
+  __device__ __forceinline__ int tokens(int k, int tid) const {
+    return min(tpl(k), max(0, (int)(size[k] / 2) - tid * tpl(k)));
+  }
+  // This lane's first byte in plane k.
+  __device__ __forceinline__ uint32_t step(int k, int tid) const {
+    if ((segmask >> k) & 1u) return 2u * (uint32_t)(tid / (kSeg / kPxPerLane));
+    return ((tokmask >> k) & 1u ? 2u * (uint32_t)tpl(k) : (uint32_t)kPxPerLane) * (uint32_t)tid;
+  }
+};
+
+// Waves per SIMD, so workgroups per compute unit: what 89 registers allow.
+constexpr int kDecompressWaves = 5;
+// Planes whose runs are placed in LDS at a time. Rendered frames seldom have
+// more that are neither raw nor one run per segment; a block that does takes
+// two rounds.
+constexpr int kValPlanes = 4;
+
+__global__ __launch_bounds__(kThreads, kDecompressWaves) void rle_decompress_kernel(const RleDArgs a) {
   // the bytes of each run-coded plane's runs at their start positions
-  __shared__ __attribute__((aligned(16))) uint8_t vals[8 * kBlock];
-  __shared__ __attribute__((aligned(16))) uint32_t starts[8][kBlock / 32];   // run-start bits
-  __shared__ uint64_t sh[12];
+  __shared__ __attribute__((aligned(16))) uint8_t vals[kValPlanes * kBlock];
+  __shared__ __attribute__((aligned(16))) uint32_t starts[kValPlanes][kBlock / 32];   // run-start bits
+  __shared__ uint32_t sh[16];
   __shared__ int32_t s_bad[3];   // a malformed block, in rotation over consecutive slots
   // byte selectors that fill a word from its run starts: for start nibble n,
   // byte j takes the word's byte at the last start <= j, else byte 3 of the
@@ -393,7 +399,8 @@ __global__ __launch_bounds__(kThreads, 4) void rle_decompress_kernel(const RleDA
     }
     fill_sel[tid] = sel;
   }
-  reinterpret_cast<u32x4*>(&starts[0][0])[tid] = u32x4{0, 0, 0, 0};
+  if (tid < kValPlanes * kBlock / 32 / 4)
+    reinterpret_cast<u32x4*>(&starts[0][0])[tid] = u32x4{0, 0, 0, 0};
   if (tid < 3) s_bad[tid] = 0;
   const int lane = tid % kWave;
 
@@ -452,218 +459,261 @@ __global__ __launch_bounds__(kThreads, 4) void rle_decompress_kernel(const RleDA
 
   uint32_t tslot = 0;   // slots with run-coded planes so far (uniform): picks the s_bad entry
   for (uint32_t g = blockIdx.x; g < total; g += gridDim.x) {
-  int tid = threadIdx.x;   // opaque per iteration (see the compressor)
-  __asm__ volatile("" : "+v"(tid));
-  const int lane = tid % kWave;
-  const uint64_t hit = __ballot(lane < a.n && g < t_incl[lane]);
-  const int s = uniform(__builtin_ctzll(hit));
-  const int b = uniform((int)(g - (t_incl[s] - t_slots[s])));
-  const RleDImg I = a.im[s];
-  uint32_t h[8];
+    int tid = threadIdx.x;   // opaque per iteration (see the compressor)
+    __asm__ volatile("" : "+v"(tid));
+    const int lane = tid % kWave, wave = uniform(tid / kWave);
+    const int q0 = tid * kPxPerLane;
+    // slot g: stream s, block b
+    const uint64_t hit = __ballot(lane < a.n && g < t_incl[lane]);
+    const int s = uniform(__builtin_ctzll(hit));
+    const int b = uniform((int)(g - (t_incl[s] - t_slots[s])));
+    const RleDImg I = a.im[s];
+    uint32_t h[8];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) h[k] = (uint32_t)uniform((int)t_hdr[s][k]);
-  const int err = uniform(t_err[s]);
-  if (err) {
-    if (tid == 0) a.status[s] = err;
-    continue;   // uniform; no LDS was touched in this slot
-  }
-  const int32_t rw = (int32_t)h[3], rh = (int32_t)h[4];
-  const int np = (int)(h[5] & 0xFFu);
-  const bool swizzled = (h[5] >> 8) & 1u;
-  const uint64_t nb = h[7];
-  if (b == 0 && a.roi_out && tid == 0)
-    reinterpret_cast<int4*>(a.roi_out)[s] = int4{(int)h[1], (int)h[2], (int)h[3], (int)h[4]};
-  if ((uint64_t)b >= nb) continue;   // uniform: a stream without blocks
-  const int64_t npx = (int64_t)rw * rh;
-  const int len = (int)imin64(kBlock, npx - (int64_t)b * kBlock);
-  // block table: uniform addresses, every lane checks the same values
-  // (three loads issued together; all inside the table the header check
-  // found readable, since np is 4 or 8 and entry nb is the first size)
-  const uint32_t* tbl = reinterpret_cast<const uint32_t*>(I.in + 32);
-  const uint32_t* srow = tbl + nb + (uint64_t)b * np;
-  const u32x4 s03 = ld_u32x4(srow);
-  const u32x4 s47 = ld_u32x4(srow + (np == 8 ? 4 : 0));
-  uint2 bo;   // boff[b], boff[b + 1]: a 4-byte aligned pair
-  __builtin_memcpy(&bo, __builtin_assume_aligned(tbl + b, 4), 8);
-  const uint32_t boff = bo.x;
-  const uint32_t bnext = bo.y;   // the first size entry when b is the last block
-  uint32_t size[8], poff[8], btotal = 0;
-  int e = 0;
+    for (int k = 0; k < 8; ++k) h[k] = (uint32_t)uniform((int)t_hdr[s][k]);
+    const int err = uniform(t_err[s]);
+    if (err) {
+      if (tid == 0) a.status[s] = err;
+      continue;   // uniform; no LDS was touched in this slot
+    }
+    if (b == 0 && a.roi_out && tid == 0)
+      reinterpret_cast<int4*>(a.roi_out)[s] = int4{(int)h[1], (int)h[2], (int)h[3], (int)h[4]};
+    const uint32_t nb = h[7];
+    if ((uint32_t)b >= nb) continue;   // uniform: a stream without blocks
+    const int32_t rw = (int32_t)h[3], rh = (int32_t)h[4];
+    const int64_t npx = (int64_t)rw * rh;
+    DBlock c;
+    c.np = (int)(h[5] & 0xFFu);
+    c.len = (int)imin64(kBlock, npx - (int64_t)b * kBlock);
+    const uint32_t len = (uint32_t)c.len, in_end = (uint32_t)imin64((int64_t)I.in_bytes, 0xFFFFFFFFll);
+    {
+      // block table: uniform addresses (three loads issued together; all
+      // inside the table the header check found readable, since np is 4 or 8
+      // and entry nb is the first size), made uniform, so that the checks and
+      // plane offsets are scalar work
+      const uint32_t* tbl = reinterpret_cast<const uint32_t*>(I.in + 32);
+      const uint32_t* srow = tbl + nb + (uint64_t)b * c.np;
+      const u32x4 v03 = ld_u32x4(srow);
+      const u32x4 v47 = ld_u32x4(srow + (c.np == 8 ? 4 : 0));
+      uint2 bo;   // boff[b], boff[b + 1]: a 4-byte aligned pair
+      __builtin_memcpy(&bo, __builtin_assume_aligned(tbl + b, 4), 8);
+      const uint32_t boff = (uint32_t)uniform((int)bo.x);
+      const uint32_t bnext = (uint32_t)uniform((int)bo.y);   // the first size entry when b is the last block
+      c.pay = (uint32_t)(rle_p0(nb, c.np) + boff);
+      c.btotal = c.tokmask = c.segmask = 0;
+      int e = 0;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    size[k] = k < 4 ? s03[k] : np == 8 ? s47[k - 4] : 0u;
-    if (k < np && (size[k] > (uint32_t)len ||
-                   (size[k] < (uint32_t)len && (size[k] == 0 || (size[k] & 1u)))))
-      e = CMP_ECORRUPT;
-    poff[k] = btotal;
-    btotal += size[k];
-  }
-  if ((boff & 15u) || (b == 0 && boff != 0)) e = CMP_ECORRUPT;
-  if ((uint64_t)b + 1 < nb && (uint64_t)bnext != boff + align16(btotal)) e = CMP_ECORRUPT;
-  // (a stream smaller than 4 GiB: all its offsets are 32-bit)
-  if (rle_p0(nb, np) + boff + align16(btotal) > imin64((int64_t)I.in_bytes, 0xFFFFFFFFll))
-    e = CMP_ECORRUPT;
-  if (e) {   // uniform; no LDS was touched in this slot
-    if (tid == 0) a.status[s] = e;
-    continue;
-  }
-  uint32_t tokmask = 0;   // planes stored as runs
-#pragma unroll
-  for (int k = 0; k < 8; ++k)
-    if (k < np && size[k] != (uint32_t)len) tokmask |= 1u << k;
-
-  // Every plane's 16-byte window of this lane, straight from the stream:
-  // the raw bytes of its 16 pixels, or its tokens (run length - 1, value).
-  // A run-coded plane of T tokens gives each lane tpl = ceil(T / 256) of
-  // them (at most 8), so that all four waves share the scatter below. A lane
-  // without bytes in a plane reads the payload's first bytes.
-  const int q0 = tid * kPxPerLane;
-  const uint32_t pay = (uint32_t)(rle_p0(nb, np) + boff);
-  const uint32_t last16 = (uint32_t)imin64((int64_t)I.in_bytes, 0xFFFFFFFFll) - 16u;
-  int tpl[8], nv[8];   // tokens per lane (uniform), this lane's tokens
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int ntok = (int)(size[k] / 2);
-    tpl[k] = uniform(max(1, (ntok + kThreads - 1) / kThreads));
-    nv[k] = min(tpl[k], max(0, ntok - tid * tpl[k]));
-  }
-  u32x4 win[8];
-  uint32_t woff[8], wsrc[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const bool tok = (tokmask >> k) & 1u;
-    const uint32_t lo = tok ? 2u * (uint32_t)tpl[k] * (uint32_t)tid : (uint32_t)q0;   // lane's byte
-    const uint32_t base = (uint32_t)uniform((int)(pay + poff[k]));
-    woff[k] = k < np && lo < size[k] ? base + lo : pay;
-    wsrc[k] = min(woff[k], last16);
-    win[k] = load16_from(I.in, wsrc[k]);   // every plane's load, unconditionally
-  }
-#pragma unroll
-  for (int k = 0; k < 8; ++k) win[k] = k < np ? load16_fix(win[k], wsrc[k], woff[k]) : u32x4{0, 0, 0, 0};
-  bool bad = false;
-  if (tokmask) {   // uniform
-    // this slot's flag; the next one's is cleared now: its last readers (two
-    // such slots ago) have all passed the previous slot's barriers
-    int32_t* bad_flag = &s_bad[tslot % 3];
-    if (tid == 0) s_bad[(tslot + 1) % 3] = 0;
-    ++tslot;
-    // start position of this lane's first token in every run-coded plane
-    uint64_t v3[3] = {0, 0, 0}, ex3[3], tot3[3];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      if (tokmask & (1u << k)) {
-        const uint32_t wv[4] = {win[k].x, win[k].y, win[k].z, win[k].w};
-        uint32_t sum = (uint32_t)nv[k];   // + the (length - 1) bytes of its tokens
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const uint32_t keep = (nv[k] > 2 * i ? 0xFFu : 0u) | (nv[k] > 2 * i + 1 ? 0xFF0000u : 0u);
-          sum = __builtin_amdgcn_sad_u8(wv[i] & keep, 0u, sum);
+      for (int k = 0; k < 8; ++k) {
+        const uint32_t sz = (uint32_t)uniform((int)(k < 4 ? v03[k] : v47[k - 4]));
+        c.size[k] = k < c.np ? sz : 0u;
+        c.poff[k] = c.btotal;
+        if (k >= c.np) continue;
+        if (sz > len || (sz < len && (sz == 0 || (sz & 1u)))) e = CMP_ECORRUPT;
+        if (sz != len) {
+          c.tokmask |= 1u << k;
+          if (sz / 2 == (len + kSeg - 1) / kSeg) c.segmask |= 1u << k;
         }
-        v3[fld_word(k)] |= (uint64_t)sum << fld_shift(k);
+        c.btotal += sz;
+      }
+      if ((boff & 15u) || (b == 0 && boff != 0)) e = CMP_ECORRUPT;
+      if ((uint32_t)b + 1 < nb && (uint64_t)bnext != boff + align16(c.btotal)) e = CMP_ECORRUPT;
+      // (a stream smaller than 4 GiB: all its offsets are 32-bit)
+      if (rle_p0(nb, c.np) + boff + align16(c.btotal) > in_end) e = CMP_ECORRUPT;
+      if (e) {   // uniform; no LDS was touched in this slot
+        if (tid == 0) a.status[s] = e;
+        continue;
       }
     }
-    block_scan_once<3>(v3, ex3, tot3, sh);
+
+    // Every plane's 16-byte window of this lane, straight from the stream: the
+    // raw bytes of its 16 pixels, its tokens (run length - 1, value), or its
+    // segment's token. A lane without bytes in a plane reads other bytes of
+    // the stream, which are not used; a window past the end of the buffer is
+    // read from its last 16 bytes and shifted into place.
+    u32x4 win[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k)
-      if ((tokmask & (1u << k)) && ((tot3[fld_word(k)] >> fld_shift(k)) & kFld) != (uint64_t)len)
-        bad = true;   // uniform
-    // each run's value at its start position, and its start bit; a run must
-    // not cross a multiple of 256 pixels
+      win[k] = load16_from(I.in, min(c.pay + c.poff[k] + c.step(k, tid), in_end - 16u));
+    if (c.pay + c.btotal + 16u > in_end || c.pay + c.btotal + 16u < c.pay) {
+      // the end of the buffer (uniform)
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      if (tokmask & (1u << k)) {
-        const uint32_t wv[4] = {win[k].x, win[k].y, win[k].z, win[k].w};
-        uint32_t pos = (uint32_t)((ex3[fld_word(k)] >> fld_shift(k)) & kFld);
-        uint8_t* vk = vals + k * kBlock;
-        uint32_t* bits = starts[k];
+      for (int k = 0; k < 8; ++k) {
+        const uint32_t lo = c.step(k, tid), off = c.pay + c.poff[k] + lo;
+        if (lo < c.size[k]) win[k] = load16_fix(win[k], min(off, in_end - 16u), off);
+      }
+    }
+    if (c.np == 4) {   // uniform
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          if (j < nv[k]) {
-            const uint32_t t = wv[j >> 1] >> (16 * (j & 1));
-            const uint32_t rl = (t & 0xFFu) + 1u;
-            if ((pos % kSeg) + rl > (uint32_t)kSeg) bad = true;
-            if (pos < (uint32_t)kBlock) {
-              vk[pos] = (uint8_t)(t >> 8);
-              __hip_atomic_fetch_or(&bits[pos >> 5], 1u << (pos & 31), __ATOMIC_RELAXED,
-                                    __HIP_MEMORY_SCOPE_WORKGROUP);
+      for (int k = 4; k < 8; ++k) win[k] = u32x4{0, 0, 0, 0};
+    }
+    if (c.tokmask) {   // uniform
+      bool bad = false;
+      // this slot's flag; the next one's is cleared now: its last readers (two
+      // such slots ago) have all passed the previous slot's barrier
+      int32_t* bad_flag = &s_bad[tslot % 3];
+      if (tid == 0) s_bad[(tslot + 1) % 3] = 0;
+      ++tslot;
+      // planes with one run per 256-pixel segment: the lane's segment is its
+      // token's value throughout, no position is needed
+      const uint32_t seg_len = min((uint32_t)kSeg, len - min(len, (uint32_t)(q0 & ~(kSeg - 1))));
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        if ((c.segmask >> k) & 1u) {
+          const uint32_t tok = win[k].x;
+          if ((uint32_t)q0 < len && (tok & 0xFFu) + 1u != seg_len) bad = true;
+          const uint32_t v = __builtin_amdgcn_perm(tok, tok, 0x01010101u);
+          win[k] = u32x4{v, v, v, v};
+        }
+      }
+      uint32_t runmask = c.tokmask & ~c.segmask;   // the other run-coded planes
+      // Start position of this lane's first token in every such plane: sums of
+      // run lengths, two 16-bit fields per word. A valid plane's fit (at most
+      // 4096); in a malformed one a field may run over into the next, but then
+      // some run of its own ends past the block, which every run is checked
+      // for below.
+      uint32_t ex4[4] = {0, 0, 0, 0};
+      if (runmask) {   // uniform
+        uint32_t v4[4] = {0, 0, 0, 0}, tot4[4];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          if ((runmask >> k) & 1u) {
+            const int tpl = c.tpl(k), nv = c.tokens(k, tid);
+            uint32_t sum = (uint32_t)nv;   // + the (length - 1) bytes of its tokens
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              if (2 * i < tpl) {   // uniform
+                const uint32_t keep = nv > 2 * i + 1 ? 0x00FF00FFu : nv > 2 * i ? 0xFFu : 0u;
+                sum = __builtin_amdgcn_sad_u8(win[k][i] & keep, 0u, sum);
+              }
             }
-            pos += rl;
+            v4[k >> 1] |= sum << (16 * (k & 1));
           }
         }
+        block_scan32_once<4>(v4, ex4, tot4, sh);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (((runmask >> k) & 1u) && ((tot4[k >> 1] >> (16 * (k & 1))) & 0xFFFFu) != len)
+            bad = true;   // uniform
       }
-    }
-    // one vote per wave into this slot's flag, then the barrier that also
-    // publishes the runs
-    if (__ballot(bad) && lane == 0)
-      __hip_atomic_fetch_or(bad_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    __syncthreads();
-    const bool block_bad = *bad_flag != 0;
-    // Expand (a malformed block skips it): a pixel takes the value of the
-    // last run start at or before it. A 256-pixel segment (the 16 lanes of
-    // one DPP row) starts with a run, so the value entering a lane comes from
-    // a scan over its row.
+      // The runs of up to kValPlanes planes at a time: each run's value at its
+      // start position, and its start bit; a run must not cross a multiple of
+      // 256 pixels nor end past the block (positions are taken modulo the
+      // block, so that a malformed one stays in it too).
+      bool block_bad = false;
+#pragma unroll 1
+      do {
+        uint32_t later = runmask;   // the planes of the next round
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      if ((tokmask & (1u << k)) && !block_bad) {
-        const u32x4 d = *reinterpret_cast<const u32x4*>(vals + k * kBlock + q0);
-        const uint32_t m = (starts[k][q0 >> 5] >> (q0 & 31)) & 0xFFFFu;
-        const uint32_t dv[4] = {d.x, d.y, d.z, d.w};
-        const int hb = 31 - __builtin_clz(m | 1u);
-        const uint32_t hw = hb < 4 ? d.x : hb < 8 ? d.y : hb < 12 ? d.z : d.w;
-        const uint32_t last = (hw >> (8 * (hb & 3))) & 0xFFu;
-        uint32_t x = m ? (0x100u | last) : 0u;
-        uint32_t y;
-        y = row_shr<1>(x); if (!(x & 0x100u)) x = y;
-        y = row_shr<2>(x); if (!(x & 0x100u)) x = y;
-        y = row_shr<4>(x); if (!(x & 0x100u)) x = y;
-        y = row_shr<8>(x); if (!(x & 0x100u)) x = y;
-        // word by word: each byte from the last start in the word, else the
-        // previous word's last byte (the value entering the lane for word 0)
-        uint32_t o[4];
-        uint32_t prev = row_shr<1>(x) << 24;
+        for (int i = 0; i < kValPlanes; ++i) later &= later - 1u;
+        const uint32_t grp = runmask & ~later;
+        uint32_t cross = 0, far = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          prev = __builtin_amdgcn_perm(prev, dv[i], fill_sel[(m >> (4 * i)) & 0xFu]);
-          o[i] = prev;
+        for (int k = 0; k < 8; ++k) {
+          if ((grp >> k) & 1u) {   // uniform
+            const int at = __builtin_popcount(grp & ((1u << k) - 1u));
+            const int tpl = c.tpl(k), nv = c.tokens(k, tid);
+            uint32_t pos = (ex4[k >> 1] >> (16 * (k & 1))) & 0xFFFFu;
+            uint8_t* vk = vals + at * kBlock;
+            uint32_t* bits = starts[at];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              if (j < tpl) {   // uniform
+                if (j < nv) {
+                  const uint32_t w = win[k][j >> 1] >> (16 * (j & 1));
+                  const uint32_t lastp = pos + (w & 0xFFu);   // the run's last pixel
+                  cross = max(cross, pos ^ lastp);
+                  far = max(far, lastp);
+                  const uint32_t p = pos & (uint32_t)(kBlock - 1);
+                  vk[p] = (uint8_t)(w >> 8);
+                  __hip_atomic_fetch_or(&bits[p >> 5], 1u << (p & 31u), __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_WORKGROUP);
+                  pos = lastp + 1u;
+                }
+              }
+            }
+          }
         }
-        win[k] = u32x4{o[0], o[1], o[2], o[3]};
+        bad = bad || cross >= (uint32_t)kSeg || far >= len;
+        // one vote per wave into this slot's flag, then the barrier that also
+        // publishes the runs
+        if (__ballot(bad) && lane == 0)
+          __hip_atomic_fetch_or(bad_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __syncthreads();
+        // Expand: a pixel takes the value of the last run start at or before
+        // it. A 256-pixel segment (the 16 lanes of one DPP row) starts with a
+        // run, so the value entering a lane comes from a scan over its row.
+        const uint32_t lane_key = ((uint32_t)lane + 1u) << 8;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          if ((grp >> k) & 1u) {
+            const int at = __builtin_popcount(grp & ((1u << k) - 1u));
+            const u32x4 d = *reinterpret_cast<const u32x4*>(vals + at * kBlock + q0);
+            const uint32_t m = (starts[at][q0 >> 5] >> (q0 & 31)) & 0xFFFFu;
+            const uint32_t dv[4] = {d.x, d.y, d.z, d.w};
+            // the lane's last start: its byte of the 16 by v_perm (selector
+            // 0x0c gives a zero byte)
+            const uint32_t hb = 31u - (uint32_t)__builtin_clz(m | 1u);
+            const uint32_t sel = (hb & 7u) | 0x0C0C0C00u;
+            const uint32_t lo = __builtin_amdgcn_perm(d.y, d.x, sel);
+            const uint32_t hi = __builtin_amdgcn_perm(d.w, d.z, sel);
+            // the nearest lane of the row with a start, as the maximum over
+            // the lanes up to this one of (lane, value)
+            uint32_t x = m ? lane_key | (hb & 8u ? hi : lo) : 0u;
+            x = max(x, row_shr<1>(x));
+            x = max(x, row_shr<2>(x));
+            x = max(x, row_shr<4>(x));
+            x = max(x, row_shr<8>(x));
+            // word by word: each byte from the last start in the word, else the
+            // previous word's last byte (the value entering the lane for word 0)
+            uint32_t prev = row_shr<1>(x) << 24;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              prev = __builtin_amdgcn_perm(prev, dv[i], fill_sel[(m >> (4 * i)) & 0xFu]);
+              win[k][i] = prev;
+            }
+          }
+        }
+        // clear this round's start bits: word q0 / 32 is read only by this
+        // lane and its neighbour in the same wave, which have both read it
+        if ((tid & 1) == 0) {
+#pragma unroll
+          for (int i = 0; i < kValPlanes; ++i) starts[i][q0 >> 5] = 0;
+        }
+        block_bad = uniform(*bad_flag) != 0;
+        runmask = later;
+        if (runmask) __syncthreads();   // the values are read
+      } while (runmask);
+      if (block_bad) {   // uniform
+        if (tid == 0) a.status[s] = CMP_ECORRUPT;
+        continue;
       }
     }
-    // clear this slot's start bits: word q0 / 32 is read only by this lane
-    // and its neighbour in the same wave, which have both read it
-    if ((tid & 1) == 0) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (tokmask & (1u << k)) starts[k][q0 >> 5] = 0;
+
+    // ---- write the pixels (row-major over the ROI), colour, then depth: byte
+    // k of pixel 4 i + j is byte j of plane k's word i (a 4 x 4 byte transpose
+    // per word). A lane holds 16 consecutive pixels, but stores are issued so
+    // that consecutive lanes write consecutive 16-byte quads: the wave's 1024
+    // pixels are restaged through LDS (the wave's quarter of every plane's run
+    // values, which only this wave reads), and in store v lane i writes pixels
+    // 256 v + 4 i .. + 3 of the wave's range (16-byte stores at a 64-byte lane
+    // stride cost four times the memory requests).
+    const int qw = (kBlock / 4) * wave + 4 * lane;   // block pixel of store 0
+    // the block's origin: the frame's top left, or its ROI's position there
+    const int64_t org = a.at_roi ? (int64_t)(int32_t)h[2] * I.pitch + (int32_t)h[1] : 0;
+    // the quad's row and column, by a 32-bit division (of the pixel's place in
+    // the block's first row where the ROI has 2^32 pixels or more)
+    const uint32_t urw = (uint32_t)rw;
+    uint32_t y0 = 0, px = (uint32_t)b * kBlock;
+    if (npx >> 32) {   // uniform
+      y0 = (uint32_t)uniform((int)((int64_t)b * kBlock / rw));
+      px = (uint32_t)((int64_t)b * kBlock - (int64_t)y0 * rw);
     }
-    if (block_bad) {   // uniform
-      if (tid == 0) a.status[s] = CMP_ECORRUPT;
-      continue;
-    }
-  }
-  // pixels from the planes: byte k of pixel 4 i + j is byte j of plane k's
-  // word i (a 4 x 4 byte transpose per word of colour and of depth)
-  uint32_t col[kPxPerLane], dep[kPxPerLane];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    transpose4x4(win[0][i], win[1][i], win[2][i], win[3][i], col[4 * i], col[4 * i + 1],
-                 col[4 * i + 2], col[4 * i + 3]);
-    transpose4x4(win[4][i], win[5][i], win[6][i], win[7][i], dep[4 * i], dep[4 * i + 1],
-                 dep[4 * i + 2], dep[4 * i + 3]);
-  }
-  if (swizzled) {
-#pragma unroll
-    for (int j = 0; j < kPxPerLane; ++j) col[j] = swizzle_bits(col[j]);
-  }
-  // ---- write the pixels (row-major over the ROI). A lane holds 16
-  // consecutive pixels, but stores are issued so that consecutive lanes
-  // write consecutive 16-byte quads: the wave's 1024 pixels are restaged
-  // through LDS (the wave's eighth of every plane's run values, which only
-  // this wave reads), and in store v lane i writes pixels 256 v + 4 i .. + 3
-  // of the wave's range (16-byte stores at a 64-byte lane stride cost four
-  // times the memory requests).
-  {
-    const int wave = tid / kWave;
+    px += (uint32_t)qw;
+    const uint32_t y = px / urw;
+    const uint32_t x0 = px - y * urw;
+    const int64_t jump = I.pitch - (int64_t)rw;   // from a row's end to the next row
+    const int64_t o0 = org + (int64_t)(y0 + y) * I.pitch + x0;
+    const bool swizzled = (h[5] >> 8) & 1u;
     uint8_t* wbase = vals + (kBlock / 4) * wave;
     // quad q of the wave (pixels 4 q ..) sits in piece q / 64 at slot
     // swz(q % 64): within each group of 8 slots (128 bytes, all banks) the
@@ -671,66 +721,73 @@ __global__ __launch_bounds__(kThreads, 4) void rle_decompress_kernel(const RleDA
     // hit 8 different 16-byte bank groups both when lane L writes its quads
     // 4 L + c and when lane i reads quad 64 v + i
     auto swz = [](int x) { return (x & ~7) | ((x + (x >> 3)) & 7); };
-    uint8_t* wl = wbase + (lane / 16) * kBlock;
+    auto write_words = [&](const u32x4& w0, const u32x4& w1, const u32x4& w2, const u32x4& w3,
+                           uint32_t* __restrict__ dst, bool unswizzle) {
+      uint8_t* wl = wbase + (lane / 16) * kBlock;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int slot = 16 * swz((4 * lane + c) % 64);
-      *reinterpret_cast<u32x4*>(wl + slot) =
-          u32x4{col[4 * c], col[4 * c + 1], col[4 * c + 2], col[4 * c + 3]};
-      if (np == 8)
-        *reinterpret_cast<u32x4*>(wl + 4 * kBlock + slot) =
-            u32x4{dep[4 * c], dep[4 * c + 1], dep[4 * c + 2], dep[4 * c + 3]};
-    }
-    __builtin_amdgcn_wave_barrier();
-    u32x4 cq[4], dq[4];
-    const int rslot = 16 * swz(lane);
+      for (int i = 0; i < 4; ++i) {
+        uint32_t p0, p1, p2, p3;
+        transpose4x4(w0[i], w1[i], w2[i], w3[i], p0, p1, p2, p3);
+        if (unswizzle) {   // uniform
+          p0 = swizzle_bits(p0);
+          p1 = swizzle_bits(p1);
+          p2 = swizzle_bits(p2);
+          p3 = swizzle_bits(p3);
+        }
+        *reinterpret_cast<u32x4*>(wl + 16 * swz((4 * lane + i) % 64)) = u32x4{p0, p1, p2, p3};
+      }
+      __builtin_amdgcn_wave_barrier();
+      u32x4 q[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      cq[v] = *reinterpret_cast<const u32x4*>(wbase + v * kBlock + rslot);
-      dq[v] = np == 8 ? *reinterpret_cast<const u32x4*>(wbase + (4 + v) * kBlock + rslot)
-                      : u32x4{0, 0, 0, 0};
-    }
-    // the block's first pixel (uniform), then the quad's by a 32-bit division
-    const int qw = (kBlock / 4) * wave + 4 * lane;   // block pixel of store 0
-    // the block's origin: the frame's top left, or its ROI's position there
-    const int64_t org = a.at_roi ? (int64_t)(int32_t)h[2] * I.pitch + (int32_t)h[1] : 0;
-    uint32_t* const ocol = I.color + org;
-    uint32_t* const odep = np == 8 ? I.depth + org : nullptr;
-    const int64_t qb = (int64_t)b * kBlock;
-    const int yb = uniform((int)(qb / rw)), xb = uniform((int)(qb - (int64_t)yb * rw));
-    const uint32_t xl = (uint32_t)xb + (uint32_t)qw;
-    const uint32_t dy = xl / (uint32_t)rw;
-    int yy = yb + (int)dy, xx = (int)(xl - dy * (uint32_t)rw);
+      for (int v = 0; v < 4; ++v)
+        q[v] = *reinterpret_cast<const u32x4*>(wbase + v * kBlock + 16 * swz(lane));
+      __builtin_amdgcn_wave_barrier();
+      int64_t o = o0;
+      uint32_t xx = x0;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int qq = qw + (kBlock / 16) * v;
-      if (qq < len) {
-        if (qq + 4 <= len && xx + 4 <= rw) {
-          const int64_t o = (int64_t)yy * I.pitch + xx;
-          st_u32x4_nt(ocol + o, cq[v]);
-          if (np == 8) st_u32x4_nt(odep + o, dq[v]);
-        } else {   // a quad at the end of a row or of the block
-          int y2 = yy, x2 = xx;
+      for (int v = 0; v < 4; ++v) {
+        const int qq = qw + (kBlock / 16) * v;
+        const uint32_t left = urw - xx;   // pixels up to the row's end
+        if (qq + 4 <= c.len && left >= 4u) {
+          st_u32x4_nt(dst + o, q[v]);
+        } else if (qq < c.len) {   // a quad at the end of a row or of the block
+          if (urw >= 4u) {         // uniform: at most one row's end in it
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (qq + j < len) {
-              const int64_t o = (int64_t)y2 * I.pitch + x2;
-              ocol[o] = cq[v][j];
-              if (np == 8) odep[o] = dq[v][j];
-              if (++x2 == rw) { x2 = 0; ++y2; }
+            for (int j = 0; j < 4; ++j)
+              if (qq + j < c.len) dst[o + j + ((uint32_t)j >= left ? jump : 0)] = q[v][j];
+          } else {
+            int64_t oj = o;
+            uint32_t xj = xx;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              if (qq + j < c.len) {
+                dst[oj] = q[v][j];
+                ++oj;
+                if (++xj == urw) {
+                  xj = 0;
+                  oj += jump;
+                }
+              }
             }
           }
         }
+        // advance 256 pixels
+        xx += kBlock / 16;
+        o += kBlock / 16;
+        if (urw >= (uint32_t)(kBlock / 16)) {   // uniform: at most one row's end
+          if (xx >= urw) {
+            xx -= urw;
+            o += jump;
+          }
+        } else {
+          const uint32_t rows = xx / urw;
+          xx -= rows * urw;
+          o += (int64_t)rows * jump;
+        }
       }
-      // advance 256 pixels
-      xx += kBlock / 16;
-      if (xx >= rw) {
-        const int d = xx / rw;
-        yy += d;
-        xx -= d * rw;
-      }
-    }
-  }
+    };
+    write_words(win[0], win[1], win[2], win[3], I.color, swizzled);
+    if (c.np == 8) write_words(win[4], win[5], win[6], win[7], I.depth, false);
   }
 }
 

@@ -51,6 +51,22 @@ def _check(sizes, rois, seed, depth, swizzle):
         assert int(n[i]) == ref.size and (streams[i][:ref.size].cpu().numpy() == ref).all(), i
         ref = oracle.rle64_compress(c, d, tuple(rois[i]))
         assert int(n64[i]) == ref.size and (s64[i][:ref.size].cpu().numpy() == ref).all(), i
+    # decoded into frames from buffers of the streams' own sizes; nothing
+    # outside the rectangles is written
+    exact = [s[:int(k)].clone() for s, k in zip(streams, n.tolist())]
+    outs = [cmp.Image(torch.full((H, W), 7, dtype=torch.int32, device=DEV),
+                      torch.full((H, W), 7, dtype=torch.int32, device=DEV) if depth else None,
+                      (0, 0, W, H)) for W, H, _ in sizes]
+    got, st = cmp.rle_decompress(exact, outs, at_roi=True)
+    torch.cuda.synchronize()
+    assert not st.any() and (got.cpu() == roi.cpu()).all()
+    for i, (c, d) in enumerate(host):
+        x, y, w, h = rois[i]
+        for t, src in ((outs[i].color, c), (outs[i].depth, d)):
+            if src is not None:
+                want = np.full(src.shape, 7, np.uint32)
+                want[y:y + h, x:x + w] = src[y:y + h, x:x + w]
+                assert (synth.as_u32(t) == want).all(), i
 
 
 @pytest.mark.parametrize("depth,swizzle", [(True, False), (False, False), (True, True)])
@@ -69,3 +85,48 @@ def test_rle_uneven_images():
     rois[5] = (7, 7, 1, 1)
     _check(sizes, rois, 5, True, False)
     _check(sizes[1:], [(0, 0, 40, 3)] * 20, 6, True, False)
+
+
+def _set_token(stream, plane, index, length):
+    """Overwrites the run length byte of a token of block 0."""
+    s = stream.copy()
+    nb, np_ = int(s[28:32].view(np.uint32)[0]), int(s[20])
+    p0 = -(-(32 + 4 * nb * (1 + np_)) // 16) * 16
+    size = s[32 + 4 * nb:32 + 4 * nb + 4 * np_].view(np.uint32)
+    s[p0 + int(size[:plane].sum()) + 2 * index] = length - 1
+    return s, int(size[plane]) // 2
+
+
+def test_rle_decode_rejects_wrong_lengths():
+    """A segment's token shorter or longer than the segment, in the first and
+    in the last (shorter) segment, and a plane whose run lengths sum to the
+    block's length plus 2^16."""
+    H, W = 3, 700   # 2100 pixels: the last segment has 52
+    color = np.zeros((H, W), np.uint32)
+    runs = np.arange(H * W) * 272 // (H * W)          # 272 runs in byte 1
+    cuts = np.concatenate([[0], np.flatnonzero(np.diff(runs)) + 1])
+    color |= (runs.reshape(H, W).astype(np.uint32) & 0xFF) << 8
+    ref = oracle.rle_compress(color, None, (0, 0, W, H))
+    bad = []
+    for index, length in ((0, 255), (3, 1), (8, 51), (8, 53), (8, 256)):
+        s, ntok = _set_token(ref, 0, index, length)
+        assert ntok == 9
+        bad.append(s)
+    # 4096 pixels: 272 whole-segment runs sum to 69632 = 4096 + 65536
+    H2, W2 = 16, 256
+    c2 = np.zeros((H2, W2), np.uint32)
+    c2 |= ((np.arange(4096) // 16).reshape(H2, W2).astype(np.uint32) & 0xFF) << 8
+    c2[0, 1:17] |= (np.arange(16, dtype=np.uint32) + 1) << 8
+    s = oracle.rle_compress(c2, None, (0, 0, W2, H2))
+    _, ntok = _set_token(s, 1, 0, 1)
+    assert ntok == 272, ntok
+    for i in range(ntok):
+        s, _ = _set_token(s, 1, i, 256)
+    print("[gpu case] rle wrong lengths", flush=True)
+    streams = [torch.from_numpy(x.copy()).to(DEV) for x in [ref] + bad + [s]]
+    outs = [cmp.Image(torch.zeros((H2, W), dtype=torch.int32, device=DEV), None, (0, 0, W, H2))
+            for _ in streams]
+    _, st = cmp.rle_decompress(streams, outs)
+    torch.cuda.synchronize()
+    assert st.cpu().tolist() == [0] + [cmp.CMP_ECORRUPT] * 6
+    assert (synth.as_u32(outs[0].color)[:H] == color).all() and cuts.size == 272
