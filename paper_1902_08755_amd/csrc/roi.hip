@@ -65,6 +65,12 @@ __device__ __forceinline__ uint32_t unit_mask(u32x4 v) {
   }
 }
 
+// 16 bytes at any 4-byte aligned address, non-temporal (read once).
+__device__ __forceinline__ u32x4 ld_unit(const uint8_t* p) {
+  const u32x4u v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4u*)p);
+  return u32x4{v.x, v.y, v.z, v.w};
+}
+
 template <int MODE>
 __device__ __forceinline__ uint32_t px_mask(const uint8_t* row, int x) {
   if constexpr (MODE == 0 || MODE == 1) {
@@ -93,73 +99,66 @@ __global__ __launch_bounds__(kThreads) void roi_kernel(const RoiArgs a) {
   const uint8_t* base =
       reinterpret_cast<const uint8_t*>(MODE == 0 ? (const void*)I.depth : I.color);
   const int64_t row_bytes = I.pitch * bpp;
-  // 16-byte units per row, and whether the row start is 16-byte aligned
-  const bool aligned = ((reinterpret_cast<uintptr_t>(base) | (uintptr_t)row_bytes) & 15) == 0;
-  const int full_units = aligned ? I.w / ppu : 0;
-  const int tail = I.w - full_units * ppu;   // pixels handled one by one
-
   int minx = 0x7FFFFFFF, miny = 0x7FFFFFFF, maxx = -1, maxy = -1;
   const int nrows = y1 - y0;
-  // Full 16-byte units, flat over (row, unit): lane t takes units t, t + 256,
-  // ...; kRoiBatch loads are issued unconditionally (an index past the end
-  // reads unit 0 of the band instead and is ignored) so they are all in
-  // flight before the first is examined.
-  const int uwork = full_units * nrows;
-  if (uwork > 0) {
-    const int dq = kThreads / full_units, dr = kThreads - dq * full_units;
-    int ry = (int)threadIdx.x / full_units;
-    int u = (int)threadIdx.x - ry * full_units;
-    for (int t0 = threadIdx.x; t0 < uwork; t0 += kThreads * kRoiBatch) {
-      u32x4 v[kRoiBatch];
-      int xs[kRoiBatch], ys[kRoiBatch];
-#pragma unroll
-      for (int k = 0; k < kRoiBatch; ++k) {
-        const bool ok = t0 + k * kThreads < uwork;
-        xs[k] = ok ? u * ppu : -1;
-        ys[k] = y0 + ry;
-        const u32x4* row =
-            reinterpret_cast<const u32x4*>(base + (int64_t)(y0 + (ok ? ry : 0)) * row_bytes);
-        v[k] = __builtin_nontemporal_load(&row[ok ? u : 0]);   // read once
-        u += dr;
-        ry += dq;
-        if (u >= full_units) { u -= full_units; ++ry; }
-      }
-#pragma unroll
-      for (int k = 0; k < kRoiBatch; ++k) {
-        const uint32_t m = xs[k] >= 0 ? unit_mask<MODE>(v[k]) : 0u;
-        if (m) {
-          minx = min(minx, xs[k] + (int)__builtin_ctz(m));
-          maxx = max(maxx, xs[k] + 31 - (int)__builtin_clz(m));
-          miny = min(miny, ys[k]);
-          maxy = max(maxy, ys[k]);
-        }
-      }
-    }
-  }
-  // The remaining pixels of each row (all of them when rows are not 16-byte
-  // aligned), one load per pixel, batched the same way.
-  const int twork = tail * nrows;
-  for (int t0 = threadIdx.x; t0 < twork; t0 += kThreads * kRoiBatch) {
-    uint32_t m[kRoiBatch];
+  if (I.w >= ppu) {   // uniform
+    // 16-byte units, flat over (row, unit): lane t takes units t, t + 256, ...
+    // A row's last unit ends at the row's end, over pixels of the one before
+    // it if the width is no multiple of a unit's (a box does not mind), and
+    // units start at any pixel, so that odd widths and pitches are read as
+    // the others are (24 frames of 1279x719, which were read pixel by pixel:
+    // 37.3 -> 19 us). kRoiBatch units are in flight per lane: each one's place
+    // is loaded again as soon as it is examined; an index past the end reads
+    // the band's first unit instead and is ignored.
+    const int units = (I.w + ppu - 1) / ppu;
+    const int uwork = units * nrows;
+    const int dq = kThreads / units, dr = kThreads - dq * units;
+    int ry = (int)threadIdx.x / units;
+    int u = (int)threadIdx.x - ry * units;
+    int t = threadIdx.x;
+    u32x4 v[kRoiBatch];
     int xs[kRoiBatch], ys[kRoiBatch];
-#pragma unroll
-    for (int k = 0; k < kRoiBatch; ++k) {
-      const int t = t0 + k * kThreads;
-      const bool ok = t < twork;
-      const int tc = ok ? t : 0;
-      const int r = tc / tail;
-      xs[k] = full_units * ppu + (tc - r * tail);
-      ys[k] = y0 + r;
-      const uint32_t mm = px_mask<MODE>(base + (int64_t)(y0 + r) * row_bytes, xs[k]);
-      m[k] = ok ? mm : 0u;
-    }
-#pragma unroll
-    for (int k = 0; k < kRoiBatch; ++k) {
-      if (m[k]) {
-        minx = min(minx, xs[k]);
-        maxx = max(maxx, xs[k]);
+    auto issue = [&](int k) {
+      const bool ok = t < uwork;
+      const int x = min(u * ppu, I.w - ppu);
+      xs[k] = ok ? x : -1;
+      ys[k] = y0 + ry;
+      v[k] = ld_unit(base + (int64_t)(y0 + (ok ? ry : 0)) * row_bytes + (ok ? x : 0) * bpp);
+      t += kThreads;
+      u += dr;
+      ry += dq;
+      if (u >= units) { u -= units; ++ry; }
+    };
+    auto examine = [&](int k) {
+      const uint32_t m = xs[k] >= 0 ? unit_mask<MODE>(v[k]) : 0u;
+      if (m) {
+        minx = min(minx, xs[k] + (int)__builtin_ctz(m));
+        maxx = max(maxx, xs[k] + 31 - (int)__builtin_clz(m));
         miny = min(miny, ys[k]);
         maxy = max(maxy, ys[k]);
+      }
+    };
+#pragma unroll
+    for (int k = 0; k < kRoiBatch; ++k) issue(k);
+    const int rounds = (uwork + kThreads * kRoiBatch - 1) / (kThreads * kRoiBatch);
+    for (int r = 1; r < rounds; ++r) {
+#pragma unroll
+      for (int k = 0; k < kRoiBatch; ++k) {
+        examine(k);
+        issue(k);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kRoiBatch; ++k) examine(k);
+  } else {
+    // an image narrower than a unit: pixel by pixel
+    for (int t = threadIdx.x; t < I.w * nrows; t += kThreads) {
+      const int r = t / I.w, x = t - r * I.w;
+      if (px_mask<MODE>(base + (int64_t)(y0 + r) * row_bytes, x)) {
+        minx = min(minx, x);
+        maxx = max(maxx, x);
+        miny = min(miny, y0 + r);
+        maxy = max(maxy, y0 + r);
       }
     }
   }
@@ -230,20 +229,46 @@ __global__ __launch_bounds__(kThreads) void roi_kernel(const RoiArgs a) {
   }
 }
 
-// Rows per workgroup: about 128 KiB of reads per workgroup, and at most
+// Rows per workgroup: about `band` bytes of reads per workgroup, and at most
 // kRoiSlotsMax workgroups per image (the slots its last workgroup folds).
 constexpr int kRoiSlotsMax = 1024;
-static int roi_rows(const cmp_image& I, int bpp) {
+constexpr int64_t kRoiBand = 128 * 1024;
+static int roi_rows(const cmp_image& I, int bpp, int64_t band) {
   const int64_t row_bytes = (int64_t)(I.roi.w > 0 ? I.roi.w : 1) * bpp;
-  int64_t r = (128 * 1024 + row_bytes - 1) / row_bytes;
+  int64_t r = (band + row_bytes - 1) / row_bytes;
   r = std::max<int64_t>(r, ((int64_t)I.roi.h + kRoiSlotsMax - 1) / kRoiSlotsMax);
   if (r < 1) r = 1;
   if (r > I.roi.h) r = I.roi.h > 0 ? I.roi.h : 1;
   return (int)r;
 }
 
-// Workgroups of a launch over images [0, n): an empty image takes one.
-static int64_t roi_workgroups(const cmp_image* imgs, int n, int bpp) {
+// The band of an image: a sixty-fourth of it, between 32 KiB (of 4-byte
+// pixels) and 128 KiB. Smaller bands spread a small image over more of the
+// chip (5 images of 575x500: 18.4 us with 128 KiB, 7.1 with 32 KiB); a large
+// one has workgroups enough, and more of them queue on its ticket (one image
+// of 3840x2160: 11.5 us with 128 KiB, 15.8 with 32 KiB). The floor grows with
+// the pixel, so that no format needs more slots than 16-byte pixels in bands
+// of 128 KiB, which cmp_roi_workspace_size counts. A launch of more than 1250
+// such bands takes larger ones, about 1000 in all: they start together, and
+// none waits for a place (48 images of 3840x2160, 1.6 GB: 265 -> 242 us, 6.6
+// TB/s, the rate of the read probe; with 2000 bands 249).
+constexpr int64_t kRoiBands = 1000;
+static int64_t roi_band(const cmp_image& I, int bpp, int64_t total) {
+  const int64_t bytes = (int64_t)I.roi.w * I.roi.h * bpp;
+  if (total / kRoiBands > kRoiBand + kRoiBand / 4) return total / kRoiBands;
+  return std::min<int64_t>(kRoiBand, std::max<int64_t>(bytes / 64, kRoiBand / 16 * bpp));
+}
+static int64_t roi_bytes(const cmp_image* imgs, int n, int bpp) {
+  int64_t b = 0;
+  for (int i = 0; i < n; ++i)
+    if (rect_valid(imgs[i].roi)) b += (int64_t)imgs[i].roi.w * imgs[i].roi.h * bpp;
+  return b;
+}
+
+// Workgroups of a launch over images [0, n) in bands of kRoiBand (`fine`:
+// of roi_band): an empty image takes one.
+static int64_t roi_workgroups(const cmp_image* imgs, int n, int bpp, bool fine) {
+  const int64_t total = roi_bytes(imgs, n, bpp);
   int64_t wg = 0;
   for (int i = 0; i < n; ++i) {
     const cmp_image& I = imgs[i];
@@ -251,7 +276,7 @@ static int64_t roi_workgroups(const cmp_image* imgs, int n, int bpp) {
       wg += 1;
       continue;
     }
-    const int rows = roi_rows(I, bpp);
+    const int rows = roi_rows(I, bpp, fine ? roi_band(I, bpp, total) : kRoiBand);
     wg += (I.roi.h + rows - 1) / rows;
   }
   return wg;
@@ -338,7 +363,7 @@ using namespace cmp;
 extern "C" size_t cmp_roi_workspace_size(const cmp_image* imgs, int32_t n) {
   if (n < 0 || (n > 0 && !imgs)) return 0;
   // 16-byte pixels give the most workgroups
-  return kRoiTickets + sizeof(int4) * (size_t)roi_workgroups(imgs, n, 16);
+  return kRoiTickets + sizeof(int4) * (size_t)roi_workgroups(imgs, n, 16, false);
 }
 
 extern "C" cmp_status cmp_roi_detect(const cmp_image* imgs, int32_t n, cmp_format fmt,
@@ -364,6 +389,10 @@ extern "C" cmp_status cmp_roi_detect(const cmp_image* imgs, int32_t n, cmp_forma
   RoiArgs a;
   memset(&a, 0, sizeof a);
   int64_t wg = 0;
+  const int64_t total = roi_bytes(imgs, n, bpp);
+  // a workspace too small for the finer bands is used with the coarse ones
+  const bool fine =
+      ws_bytes >= kRoiTickets + sizeof(int4) * (size_t)roi_workgroups(imgs, n, bpp, true);
   for (int i = 0; i < n; ++i) {
     const cmp_image& I = imgs[i];
     CMP_REQUIRE(rect_valid(I.roi), "imgs[%d] has a negative size", i);
@@ -374,7 +403,7 @@ extern "C" cmp_status cmp_roi_detect(const cmp_image* imgs, int32_t n, cmp_forma
       const uintptr_t p = (uintptr_t)(mode == 0 ? (const void*)I.depth : I.color);
       CMP_REQUIRE(p % (uintptr_t)(bpp < 16 ? bpp : 16) == 0, "imgs[%d]: misaligned buffer", i);
     }
-    const int rows = empty ? 1 : roi_rows(I, bpp);
+    const int rows = empty ? 1 : roi_rows(I, bpp, fine ? roi_band(I, bpp, total) : kRoiBand);
     const int nwg = empty ? 1 : (I.roi.h + rows - 1) / rows;
     a.im[i] = RoiImg{I.color, I.depth, I.pitch, empty ? 0 : I.roi.w, empty ? 0 : I.roi.h,
                      (int32_t)wg, nwg, rows, 0};
