@@ -196,9 +196,13 @@ cmp_status cmp_composite_over(const cmp_image* in, int32_t n, cmp_format fmt,
  *                  bytes (0, and NULL allowed, for n <= 64): the layer
  *                  descriptors of a pass with more layers. Calls sharing a
  *                  workspace must not overlap.
- * The layers are visited in chunks of 32 positions: with more than 32, the
- * alpha of the layers in front of the back chunk is read once more (a first
- * pass that keeps the transmittance at every chunk's front edge).
+ * The layers that reach a pixel's row segment (64 pixels) are visited in
+ * groups of 32: with more than 32, the alpha of the layers in front of the
+ * back group is read once more (a first pass that keeps the transmittance in
+ * front of every group).
+ * _as: gradients in format grad_fmt, CMP_RGBA32F (4 floats per pixel, 16-byte
+ * aligned) or CMP_RGBA16F (4 halves, 8-byte aligned: the FP32 result rounded
+ * to nearest once more); pitches in pixels either way.
  * n <= 256. Errors: CMP_EINVAL, CMP_ENOSPC (workspace), CMP_EUNSUPPORTED
  * (n > 256), CMP_EHIP.
  */
@@ -209,6 +213,12 @@ cmp_status cmp_composite_over_backward(const cmp_image* in, int32_t n, cmp_forma
                                        float* const* grad_layers,
                                        const int64_t* grad_pitch_layers, void* workspace,
                                        size_t ws_bytes, void* stream);
+cmp_status cmp_composite_over_backward_as(const cmp_image* in, int32_t n, cmp_format fmt,
+                                          const int32_t* order_b2f, cmp_rect viewport,
+                                          const float* grad_out, int64_t grad_pitch,
+                                          void* const* grad_layers, cmp_format grad_fmt,
+                                          const int64_t* grad_pitch_layers, void* workspace,
+                                          size_t ws_bytes, void* stream);
 
 /*
  * Subpixel compositing (Section 4.2.3, Subpixel: the default compositing

@@ -88,6 +88,8 @@ def lib() -> ctypes.CDLL:
         "cmp_assemble_pixels": ([IMG, i32, P, i32, i32, Rect, P, i64, P], i32),
         "cmp_composite_over": ([IMG, i32, i32, P, Rect, P, i64, Schedule, Tile, P], i32),
         "cmp_composite_over_backward": ([IMG, i32, i32, P, Rect, P, i64, P, P, P, sz, P], i32),
+        "cmp_composite_over_backward_as": ([IMG, i32, i32, P, Rect, P, i64, P, i32, P, P, sz, P],
+                                           i32),
         "cmp_over_backward_workspace_size": ([i32], sz),
         "cmp_roi_workspace_size": ([IMG, i32], sz),
         "cmp_roi_detect": ([IMG, i32, i32, P, P, sz, P], i32),
@@ -239,24 +241,30 @@ def composite_over(layers: Sequence, order, viewport, out=None, schedule=("seq",
 
 
 def composite_over_backward(layers: Sequence, order, viewport, grad_out, grads=None, stream=None):
-    """Adjoint of composite_over: d loss / d layer for every layer."""
+    """Adjoint of composite_over: d loss / d layer for every layer, in FP32, or
+    in FP16 where all of ``grads`` are float16 tensors."""
     n = len(layers)
     rgba = [l.rgba if hasattr(l, "rgba") else l.color for l in layers]
     fmt = _fmt_of(rgba[0]) if n else RGBA32F
     if grads is None:
         grads = [torch.empty((int(l.roi[3]), int(l.roi[2]), 4), dtype=torch.float32,
                              device=r.device) for l, r in zip(layers, rgba)]
+    half = sum(g.dtype == torch.float16 for g in grads)
+    if half not in (0, len(grads)):
+        raise ValueError("grads mix float16 with other types")
     ptrs = (ctypes.c_void_p * max(1, n))(*[g.data_ptr() for g in grads])
     pitches = (ctypes.c_int64 * max(1, n))(*[_rgba_pitch(g) for g in grads])
     order_arr = (ctypes.c_int32 * max(1, n))(*[int(v) for v in order])
     grad_out = grad_out.contiguous()
     need = lib().cmp_over_backward_workspace_size(n)
     ws = workspace("over_backward", need) if need else None
-    st = lib().cmp_composite_over_backward(_images(layers, "rgba"), n, fmt, order_arr,
-                                           _rect(viewport), grad_out.data_ptr(),
-                                           _rgba_pitch(grad_out), ptrs, pitches,
-                                           ws.data_ptr() if ws is not None else None,
-                                           ws.numel() if ws is not None else 0, _stream(stream))
+    st = lib().cmp_composite_over_backward_as(_images(layers, "rgba"), n, fmt, order_arr,
+                                              _rect(viewport), grad_out.data_ptr(),
+                                              _rgba_pitch(grad_out), ptrs,
+                                              RGBA16F if half else RGBA32F, pitches,
+                                              ws.data_ptr() if ws is not None else None,
+                                              ws.numel() if ws is not None else 0,
+                                              _stream(stream))
     _check(st, "cmp_composite_over_backward")
     return grads
 
@@ -281,6 +289,15 @@ class OverComposite(torch.autograd.Function):
     def backward(ctx, grad_out):
         layers = ctx.saved_tensors
         imgs = [Image(l.detach(), None, r) for l, r in zip(layers, ctx.rois)]
+        dtype = layers[0].dtype if layers else torch.float32
+        if all(l.dtype == dtype and l.shape[0] == int(r[3]) and l.shape[1] >= int(r[2])
+               for l, r in zip(layers, ctx.rois)):
+            # the kernel writes each gradient in its layer's type and shape
+            # (zeros beside the ROI of a layer stored with a wider pitch)
+            grads = [(torch.empty if l.shape[1] == int(r[2]) else torch.zeros)(
+                l.shape, dtype=dtype, device=l.device) for l, r in zip(layers, ctx.rois)]
+            composite_over_backward(imgs, ctx.order, ctx.viewport, grad_out.float(), grads)
+            return (None, None, None, *grads)
         grads = composite_over_backward(imgs, ctx.order, ctx.viewport, grad_out.float())
         out = []
         for l, g in zip(layers, grads):

@@ -91,18 +91,6 @@ __device__ __forceinline__ void st_u32x4(uint32_t* p, u32x4 v) {
   __builtin_memcpy(__builtin_assume_aligned(p, 4), &v, 16);
 }
 
-// One RGBA pixel of a float layer as float4 (RGBA32F: 16-byte aligned load;
-// RGBA16F: 8-byte aligned load, exact widening).
-template <int FMT>
-__device__ __forceinline__ f32x4 ld_rgba(const void* base, int64_t px) {
-  if constexpr (FMT == CMP_RGBA32F) {
-    return reinterpret_cast<const f32x4*>(base)[px];
-  } else {
-    const f16x4 h = reinterpret_cast<const f16x4*>(base)[px];
-    return f32x4{(float)h.x, (float)h.y, (float)h.z, (float)h.w};
-  }
-}
-
 __device__ __forceinline__ int wave_min(int v) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) v = min(v, __shfl_xor(v, m));
@@ -142,6 +130,22 @@ __device__ __forceinline__ int segment_of(F begin_of, int n, int blk) {
   if (n <= 1) return 0;
   if (n <= 16) return count_begins_le<16>(begin_of, n, blk);
   return count_begins_le<64>(begin_of, n, blk);
+}
+
+// Orders a wave's own LDS accesses for the compiler (the hardware runs them in
+// order): lanes read what other lanes of the wave wrote.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Which tile workgroup blk takes: workgroups go to the 8 XCDs in turn, so runs
+// of `chunk` consecutive tiles are dealt to one XCD each, whose L2 then holds
+// the cache lines that neighbouring tiles share.
+__device__ __forceinline__ int xcd_tile(int blk, int total, int chunk) {
+  const int group = 8 * chunk, base = blk / group * group, r = blk - base;
+  return base + group <= total ? base + (r % 8) * chunk + r / 8 : blk;
 }
 
 // The placement of contributor i: the host rectangle, or the device one

@@ -3,6 +3,8 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "over_tile.hpp"
 
 namespace cmp {
@@ -58,25 +60,32 @@ __global__ __launch_bounds__(kThreads) void over_tree_kernel(const OverArgs a) {
 // For the pixel's covering layers in front-to-back order i, with
 // T_0 = 1, T_{i+1} = T_i (1 - a_i) and S_i = L_i + (1 - a_i) S_{i+1}:
 //     grad L_i = G T_i,   grad a_i += -T_i <G, S_{i+1}>.
-// The positions (back to front) are taken in chunks of kChunk. Per chunk, a
-// back-to-front sweep reads every layer once, carries S (FP64) and keeps
-// a_i and D_i = <G, S_{i+1}> per lane in LDS; a front-to-back sweep then
-// forms T (FP64) from the kept a_i and writes the gradients. Nothing per
-// layer goes to memory. The chunks run back to front, so S carries over;
-// the transmittance in front of each chunk (a checkpoint) comes from a first
-// pass over the alpha of the layers in front of the back chunk, front to
-// back, kept per lane in LDS (FP64). Only layers that reach the tile are
-// visited, kOverBatch of them per batch of unconditional loads (a lane the
-// layer does not cover reads the layer's first pixel and discards it).
-constexpr int kChunk = 32;
+// As in the forward pass a wave takes 64 pixels of a row at a time. It lists
+// the layers that reach them, back to front, in LDS (the address of the first
+// pixel in the layer and in its gradient, and the covered lanes), and takes
+// the list in groups of kGroup. Per group, a back-to-front sweep reads every
+// layer once, carries S (FP64) and keeps a_i and D_i = <G, S_{i+1}> in
+// registers; a front-to-back sweep then forms T (FP64) from the kept a_i and
+// writes the gradients. Nothing per layer goes to memory. The groups run back
+// to front, so S carries over; the transmittance in front of each group (a
+// checkpoint) comes from a first pass over the alpha of the groups in front
+// of the back one, front to back.
+// What bounds it: memory. Where every layer covers every pixel, half of the
+// bytes are writes (32 FP32 layers of 1024x1024, 1.09 GB: 188 us, 5.8 TB/s,
+// where a copy reaches 5.0). Two waves per SIMD, which a_i and D_i in registers
+// leave, are enough for it (D_i in LDS and four waves: 191 us). The groups are
+// of the layers that a row segment meets, not of list positions: of 80 partial
+// FP16 layers it meets about 20, and positions took three groups and two
+// readings of most alphas (961x541: 270 us and one zeroing launch per layer
+// that reaches out of the view, 430 us in all; now 77).
+constexpr int kGroup = 32;
 constexpr int kBwdInline = 64;                        // descriptors in the kernel arguments
 constexpr int kBwdMaxLayers = 256;                    // with a descriptor workspace
-constexpr int kBwdCkpt = kBwdMaxLayers / kChunk - 1;  // checkpoints of the general kernel
-constexpr int kBwdMaxChunks = kBwdMaxLayers / kChunk;
+constexpr int kBwdCkpt = kBwdMaxLayers / kGroup - 1;  // checkpoints of the general kernel
 
 struct BwdDesc {
   const void* color;
-  float* grad;
+  void* grad;
   int64_t pitch;
   int64_t gpitch;
   int32_t x, y, w, h;
@@ -93,38 +102,45 @@ struct BwdArgs {
 };
 static_assert(sizeof(BwdArgs) <= 4096, "kernel arguments must fit in 4 KiB");
 
-__device__ __forceinline__ bool covers(const BwdDesc& D, int X, int Y) {
-  return X >= D.x && X < D.x + D.w && Y >= D.y && Y < D.y + D.h;
+// A listed layer: the segment's first pixel in it and in its gradient, and
+// its covered lanes (OverSeg).
+struct BwdSeg {
+  uint32_t lo, hi, span, glo, ghi;
+};
+
+typedef const __attribute__((address_space(1))) char* GlobalBytes;
+__device__ __forceinline__ uint32_t lane_of(uint32_t v, int i) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, i);
+}
+__device__ __forceinline__ GlobalBytes lane_address(uint32_t lo, uint32_t hi, int i) {
+  return (GlobalBytes)(((uint64_t)lane_of(hi, i) << 32) | lane_of(lo, i));
 }
 
-template <int FMT>
-__device__ __forceinline__ float ld_alpha(const void* base, int64_t px) {
-  if constexpr (FMT == CMP_RGBA32F) {
-    return ((const __attribute__((address_space(1))) float*)base)[4 * px + 3];
-  } else {
-    return (float)((const __attribute__((address_space(1))) _Float16*)base)[4 * px + 3];
-  }
+// FP32 to FP16. Without the pragma the FP64 value behind v is rounded to FP16
+// at once, which is not the FP32 gradient rounded where that one is a tie.
+__device__ __forceinline__ f16x4 narrow(f32x4 v) {
+#pragma clang fp contract(off)
+  return f16x4{(_Float16)v.x, (_Float16)v.y, (_Float16)v.z, (_Float16)v.w};
 }
 
-// T <- T * prod (1 - a_j) over the hit positions of [j0, j0 + 32), front to
-// back (descending positions).
+// T <- T * prod (1 - a_j) over the m layers of a group, front to back.
 template <int FMT>
-__device__ __forceinline__ double bwd_alpha_product(const BwdDesc* __restrict__ d, int j0,
-                                                    uint32_t hits, int X, int Y, double T) {
-  while (hits) {   // uniform
+__device__ __forceinline__ double bwd_alpha_product(const BwdSeg& sg, int m, int lane, double T) {
+  constexpr uint32_t bpp = FMT == CMP_RGBA32F ? 16 : 8;
+  for (int i1 = m; i1 > 0; i1 -= kOverBatch) {   // uniform
     float al[kOverBatch];
     bool cov[kOverBatch];
-    const int first = 31 - __builtin_clz(hits);
 #pragma unroll
     for (int k = 0; k < kOverBatch; ++k) {
-      const bool has = hits != 0;
-      const int i = has ? 31 - __builtin_clz(hits) : first;
-      hits &= ~(1u << i);
-      const BwdDesc& D = d[j0 + i];
-      const int dx = uniform(D.x), dy = uniform(D.y), dw = uniform(D.w), dh = uniform(D.h);
-      cov[k] = has && X >= dx && X < dx + dw && Y >= dy && Y < dy + dh;
-      al[k] = ld_alpha<FMT>(uniform_ptr(D.color),
-                            cov[k] ? (int64_t)(Y - dy) * uniform64(D.pitch) + (X - dx) : 0);
+      const int i = max(i1 - 1 - k, 0);
+      const uint32_t span = lane_of(sg.span, i), c0 = span & 0xFFu;
+      cov[k] = i1 - 1 - k >= 0 && (uint32_t)lane - c0 < (span >> 8);
+      const GlobalBytes p =
+          lane_address(sg.lo, sg.hi, i) + (cov[k] ? (uint32_t)lane : c0) * bpp + bpp / 4 * 3;
+      if constexpr (FMT == CMP_RGBA32F)
+        al[k] = *(const __attribute__((address_space(1))) float*)p;
+      else
+        al[k] = (float)*(const __attribute__((address_space(1))) _Float16*)p;
     }
 #pragma unroll
     for (int k = 0; k < kOverBatch; ++k)
@@ -133,122 +149,137 @@ __device__ __forceinline__ double bwd_alpha_product(const BwdDesc* __restrict__ 
   return T;
 }
 
-// One chunk: positions j0 + i for the set bits i of `hits`. S (in/out) is the
-// composite of everything behind the chunk; T is the transmittance in front
-// of it.
-template <int FMT>
-__device__ __forceinline__ void bwd_chunk(const BwdDesc* __restrict__ d, int j0, uint32_t hits,
-                                          int X, int Y, const f32x4 G, double (&S)[4], double T,
-                                          float2 (*st)[kThreads]) {
+// One group: the m layers of lanes 0 .. m - 1 of sg, back to front. S (in and
+// out) is the composite of everything behind the group; T is the
+// transmittance in front of it. GFMT: the format of the gradients, rounded
+// once more from FP32 if it is FP16.
+template <int FMT, int GFMT>
+__device__ __forceinline__ void bwd_group(const BwdSeg& sg, int m, int lane, const f32x4 G,
+                                          double (&S)[4], double T) {
+  constexpr uint32_t bpp = FMT == CMP_RGBA32F ? 16 : 8, gbpp = GFMT == CMP_RGBA32F ? 16 : 8;
+  typedef typename RawPx<FMT>::type Raw;
+  typedef const __attribute__((address_space(1))) Raw* GPtr;
   const double g0 = G.x, g1 = G.y, g2 = G.z, g3 = G.w;
-  const int tid = threadIdx.x;
-  uint32_t m = hits;
-  while (m) {   // uniform: back to front over the hit positions
-    f32x4 L[kOverBatch];
-    bool cov[kOverBatch], has[kOverBatch];
-    int pos[kOverBatch];
-    const int first = (int)__builtin_ctz(m);
+  float al[kGroup], dd[kGroup];   // alpha 0 leaves T unchanged
+#pragma unroll
+  for (int b = 0; b < kGroup; b += kOverBatch) {
+    if (b >= m) break;   // uniform
+    Raw L[kOverBatch];
+    bool cov[kOverBatch];
 #pragma unroll
     for (int k = 0; k < kOverBatch; ++k) {
-      has[k] = m != 0;
-      pos[k] = has[k] ? (int)__builtin_ctz(m) : first;
-      m &= m - 1u;
-      const BwdDesc& D = d[j0 + pos[k]];
-      const int dx = uniform(D.x), dy = uniform(D.y), dw = uniform(D.w), dh = uniform(D.h);
-      cov[k] = has[k] && X >= dx && X < dx + dw && Y >= dy && Y < dy + dh;
-      L[k] = widen(ld_raw<FMT>(uniform_ptr(D.color),
-                               cov[k] ? (int64_t)(Y - dy) * uniform64(D.pitch) + (X - dx) : 0));
+      const int i = b + k < m ? b + k : b;
+      const uint32_t span = lane_of(sg.span, i), c0 = span & 0xFFu;
+      cov[k] = b + k < m && (uint32_t)lane - c0 < (span >> 8);
+      const uint32_t off = (cov[k] ? (uint32_t)lane : c0) * bpp;
+      L[k] = __builtin_nontemporal_load((GPtr)(lane_address(sg.lo, sg.hi, i) + off));
     }
 #pragma unroll
     for (int k = 0; k < kOverBatch; ++k) {
-      if (!has[k]) break;   // uniform
-      float2 e = make_float2(0.f, 0.f);   // (alpha, D); alpha 0 leaves T unchanged
+      al[b + k] = dd[b + k] = 0.f;
       if (cov[k]) {
-        e.y = (float)(g0 * S[0] + g1 * S[1] + g2 * S[2] + g3 * S[3]);
-        e.x = L[k].w;
-        const double t = 1.0 - (double)L[k].w;
-        S[0] = (double)L[k].x + t * S[0];
-        S[1] = (double)L[k].y + t * S[1];
-        S[2] = (double)L[k].z + t * S[2];
-        S[3] = (double)L[k].w + t * S[3];
+        const f32x4 v = widen(L[k]);
+        dd[b + k] = (float)(g0 * S[0] + g1 * S[1] + g2 * S[2] + g3 * S[3]);
+        al[b + k] = v.w;
+        const double t = 1.0 - (double)v.w;
+        S[0] = (double)v.x + t * S[0];
+        S[1] = (double)v.y + t * S[1];
+        S[2] = (double)v.z + t * S[2];
+        S[3] = (double)v.w + t * S[3];
       }
-      st[pos[k]][tid] = e;
     }
   }
-  m = hits;
-  while (m) {   // uniform: front to back
-    const int i = 31 - __builtin_clz(m);
-    m &= ~(1u << i);
-    const BwdDesc& Dd = d[j0 + i];
-    if (!covers(Dd, X, Y)) continue;
-    const float2 e = st[i][tid];
-    f32x4 g;
-    g.x = (float)(g0 * T);
-    g.y = (float)(g1 * T);
-    g.z = (float)(g2 * T);
-    g.w = (float)(g3 * T - T * (double)e.y);
-    // a global-address-space store cannot alias the kernel-argument copy
-    __builtin_nontemporal_store(g, &((__attribute__((address_space(1))) f32x4*)(Dd.grad))
-        [(int64_t)(Y - Dd.y) * Dd.gpitch + (X - Dd.x)]);
-    T = T * (1.0 - (double)e.x);
+#pragma unroll
+  for (int i = kGroup - 1; i >= 0; --i) {
+    if (i >= m) continue;   // uniform: front to back
+    const uint32_t span = lane_of(sg.span, i);
+    if ((uint32_t)lane - (span & 0xFFu) < (span >> 8)) {
+      f32x4 g;
+      g.x = (float)(g0 * T);
+      g.y = (float)(g1 * T);
+      g.z = (float)(g2 * T);
+      g.w = (float)(g3 * T - T * (double)dd[i]);
+      // a global-address-space store cannot alias the kernel-argument copy
+      const GlobalBytes p = lane_address(sg.glo, sg.ghi, i) + (uint32_t)lane * gbpp;
+      if constexpr (GFMT == CMP_RGBA32F)
+        __builtin_nontemporal_store(g, (__attribute__((address_space(1))) f32x4*)p);
+      else
+        __builtin_nontemporal_store(narrow(g), (__attribute__((address_space(1))) f16x4*)p);
+      T = T * (1.0 - (double)al[i]);
+    }
   }
 }
 
-// kInline: n <= kBwdInline, descriptors in the arguments, at most two chunks
-// (the back chunk's checkpoint stays in a register); otherwise descriptors
+// kInline: n <= kBwdInline, descriptors in the arguments, at most two groups
+// (the back group's checkpoint stays in a register); otherwise descriptors
 // from the workspace and up to kBwdCkpt checkpoints in LDS.
-template <int FMT, bool kInline>
+// Tile order: an XCD takes runs of consecutive tiles, so that the cache lines
+// which neighbouring tiles share where rows are no multiple of 128 bytes are
+// read and written by one L2 (30 layers of 1023x1025: 235 us in launch order,
+// 218 in runs of 16, 206 in runs of 256), and the workgroups in flight do not
+// all meet in the same memory channels where they are (32 of 1024x1024: 199,
+// 198, 188). Below 4096 tiles runs of 256 leave the XCDs unequal shares (80
+// partial layers over 961x541, 2176 tiles: 77 us in runs of 16, 89 in runs of
+// 256).
+template <int FMT, int GFMT, bool kInline>
 __global__ __launch_bounds__(kThreads) void over_bwd_kernel(const BwdArgs a) {
-  __shared__ float2 st[kChunk][kThreads];
+  constexpr int kList = kInline ? kBwdInline : kBwdMaxLayers;
+  __shared__ uint32_t s_list[kThreads / kWave][5][kList];
   __shared__ double tck[kInline ? 1 : kBwdCkpt][kThreads];
-  __shared__ uint32_t s_hits[kBwdMaxChunks];
   const BwdDesc* d = kInline ? a.c : a.desc;
-  const int ty = blockIdx.x / a.tiles_x, tx = blockIdx.x - ty * a.tiles_x;
+  const int blk = xcd_tile((int)blockIdx.x, (int)gridDim.x, gridDim.x >= 4096 ? 256 : 16);
+  const int ty = blk / a.tiles_x, tx = blk - ty * a.tiles_x;
   const int x0 = a.vx + tx * a.tile_w, y0 = a.vy + ty * a.tile_h;
   const int tw = min(a.tile_w, a.vx + a.vw - x0), th = min(a.tile_h, a.vy + a.vh - y0);
-  const int np = tw * th;
-  const int n = a.n, nch = (n + kChunk - 1) / kChunk;
-  // each chunk's layer mask for this tile, found once, before the per-pixel
-  // loop (every lane active): wave w takes chunks w, w + 4, ...; lane i
-  // tests position i of the chunk and one ballot gives the mask
-  {
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    for (int ch = wave; ch < nch; ch += kThreads / kWave) {
-      const int j = ch * kChunk + lane;
-      bool hit = false;
-      if (lane < kChunk && j < n) {
-        const BwdDesc& D = d[j];
-        hit = !tile_misses(D.x, D.y, D.w, D.h, x0, y0, tw, th);
+  const int lane = threadIdx.x % kWave;
+  uint32_t(*list)[kList] = s_list[uniform((int)(threadIdx.x / kWave))];
+  over_segments(x0, y0, tw, th, [&](int Y, int X0, int cols) {
+    f32x4 G{0.f, 0.f, 0.f, 0.f};
+    if (lane < cols)
+      G = reinterpret_cast<const f32x4*>(
+          a.gout)[(int64_t)(Y - a.vy) * a.gout_pitch + (X0 + lane - a.vx)];
+    // the layers that reach the segment, back to front
+    int cnt = 0;
+    for (int c0 = 0; c0 < a.n; c0 += kWave) {
+      BwdDesc D{nullptr, nullptr, 0, 0, 0, 0, 0, 0};
+      if (c0 + lane < a.n) D = d[c0 + lane];
+      uint64_t hits;
+      const OverSeg s =
+          over_segment<FMT>(OverDesc{D.color, D.pitch, D.x, D.y, D.w, D.h}, X0, cols, Y, hits);
+      const uint64_t ga = over_address<GFMT>(D.grad, D.gpitch, D.x, D.y, X0, Y);
+      if ((hits >> lane) & 1u) {
+        const int at = cnt + (int)__builtin_popcountll(hits & ((1ull << lane) - 1ull));
+        list[0][at] = s.lo;
+        list[1][at] = s.hi;
+        list[2][at] = s.span;
+        list[3][at] = (uint32_t)ga;
+        list[4][at] = (uint32_t)(ga >> 32);
       }
-      const uint32_t m = (uint32_t)__ballot(hit);
-      if (lane == 0) s_hits[ch] = m;
+      cnt += (int)__builtin_popcountll(hits);
     }
-  }
-  __syncthreads();
-  for (int p = threadIdx.x; p < np; p += kThreads) {
-    const int r = p / tw;
-    const int c = p - r * tw;
-    const int X = x0 + c, Y = y0 + r;
-    const f32x4 G =
-        reinterpret_cast<const f32x4*>(a.gout)[(int64_t)(Y - a.vy) * a.gout_pitch + (X - a.vx)];
-    // checkpoints: the transmittance in front of chunks nch-2 .. 0
+    wave_lds_fence();   // a wave reads its own list only
+    const int groups = (cnt + kGroup - 1) / kGroup;
+    auto group_layers = [&](int g) {
+      const int i = g * kGroup + (lane % kGroup), j = i < cnt ? i : 0;
+      return BwdSeg{list[0][j], list[1][j], list[2][j], list[3][j], list[4][j]};
+    };
+    // checkpoints: the transmittance in front of groups `groups` - 2 .. 0
     double T1 = 1.0;
     {
       double T = 1.0;
-      for (int ch = nch - 1; ch >= 1; --ch) {
-        const int j0 = ch * kChunk;
-        T = bwd_alpha_product<FMT>(d, j0, s_hits[ch], X, Y, T);
+      for (int g = groups - 1; g >= 1; --g) {
+        T = bwd_alpha_product<FMT>(group_layers(g), min(kGroup, cnt - g * kGroup), lane, T);
         if (kInline) T1 = T;
-        else tck[ch - 1][threadIdx.x] = T;
+        else tck[g - 1][threadIdx.x] = T;
       }
     }
     double S[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int ch = 0; ch < nch; ++ch) {
-      const int j0 = ch * kChunk;
-      const double T = ch == nch - 1 ? 1.0 : kInline ? T1 : tck[ch][threadIdx.x];
-      bwd_chunk<FMT>(d, j0, s_hits[ch], X, Y, G, S, T, st);
+    for (int g = 0; g < groups; ++g) {
+      const double T = g == groups - 1 ? 1.0 : kInline ? T1 : tck[g][threadIdx.x];
+      bwd_group<FMT, GFMT>(group_layers(g), min(kGroup, cnt - g * kGroup), lane, G, S, T);
     }
-  }
+    wave_lds_fence();   // the list is read
+  });
 }
 
 // Copies up to kBwdInline descriptors from the arguments to device memory
@@ -265,13 +296,32 @@ __global__ __launch_bounds__(kThreads) void bwd_desc_kernel(const BwdDescCopy a)
   for (int i = threadIdx.x; i < a.n; i += kThreads) a.dst[i] = a.c[i];
 }
 
-__global__ __launch_bounds__(kThreads) void zero_rgba_kernel(float* p, int64_t pitch, int w,
-                                                             int h) {
-  const int64_t npx = (int64_t)w * h;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < npx;
-       i += (int64_t)gridDim.x * kThreads) {
-    const int64_t y = i / w, x = i - y * w;
-    reinterpret_cast<f32x4*>(p)[y * pitch + x] = f32x4{0.f, 0.f, 0.f, 0.f};
+// Zeroes the parts of layer gradients that the viewport does not reach, of up
+// to kBwdInline layers per launch (one launch per layer, over all of it, took
+// most of the host's time where many layers reach out of the view).
+struct ZeroLayer {
+  void* p;
+  int64_t pitch;
+  int32_t w, h;
+  int32_t ix0, iy0, ix1, iy1;   // the part inside the viewport, left alone
+};
+struct ZeroArgs {
+  ZeroLayer l[kBwdInline];
+};
+static_assert(sizeof(ZeroArgs) <= 4096, "kernel arguments must fit in 4 KiB");
+
+// A wave takes a row at a time; Px: one pixel of the gradient.
+template <typename Px>
+__global__ __launch_bounds__(kThreads) void zero_outside_kernel(const ZeroArgs a) {
+  const ZeroLayer& L = a.l[blockIdx.y];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  for (int y = (int)blockIdx.x * (kThreads / kWave) + wave; y < L.h;
+       y += (int)gridDim.x * (kThreads / kWave)) {
+    Px* row = reinterpret_cast<Px*>(L.p) + (int64_t)y * L.pitch;
+    const bool in = y >= L.iy0 && y < L.iy1;
+    const int end0 = in ? L.ix0 : L.w, begin1 = in ? L.ix1 : L.w;
+    for (int x = lane; x < end0; x += kWave) row[x] = Px{};
+    for (int x = begin1 + lane; x < L.w; x += kWave) row[x] = Px{};
   }
 }
 
@@ -395,16 +445,17 @@ extern "C" size_t cmp_over_backward_workspace_size(int32_t n) {
   return n > kBwdInline && n <= kBwdMaxLayers ? (size_t)n * sizeof(BwdDesc) : 0;
 }
 
-extern "C" cmp_status cmp_composite_over_backward(const cmp_image* in, int32_t n, cmp_format fmt,
-                                                  const int32_t* order_b2f, cmp_rect viewport,
-                                                  const float* grad_out, int64_t grad_pitch,
-                                                  float* const* grad_layers,
-                                                  const int64_t* grad_pitch_layers,
-                                                  void* workspace, size_t ws_bytes,
-                                                  void* stream) {
-  CMP_RANGE("cmp_composite_over_backward");
+static cmp_status over_backward_impl(const cmp_image* in, int32_t n, cmp_format fmt,
+                                     const int32_t* order_b2f, cmp_rect viewport,
+                                     const float* grad_out, int64_t grad_pitch,
+                                     void* const* grad_layers, cmp_format grad_fmt,
+                                     const int64_t* grad_pitch_layers, void* workspace,
+                                     size_t ws_bytes, void* stream) {
   cmp_status st = validate_over_inputs(in, n, fmt, order_b2f);
   if (st != CMP_OK) return st;
+  CMP_REQUIRE(grad_fmt == CMP_RGBA32F || grad_fmt == CMP_RGBA16F,
+              "gradient format %d is not a float format", grad_fmt);
+  const int galign = grad_fmt == CMP_RGBA32F ? 16 : 8;
   if (n > kBwdMaxLayers) {
     set_error("the backward pass supports at most %d layers", kBwdMaxLayers);
     return CMP_EUNSUPPORTED;
@@ -422,30 +473,52 @@ extern "C" cmp_status cmp_composite_over_backward(const cmp_image* in, int32_t n
   CMP_REQUIRE(n == 0 || (grad_layers && grad_pitch_layers), "grad_layers is NULL");
   for (int i = 0; i < n; ++i) {
     if (rect_empty(in[i].roi)) continue;
-    CMP_REQUIRE(grad_layers[i] && ((uintptr_t)grad_layers[i] & 15) == 0,
-                "grad_layers[%d] must be 16-byte aligned", i);
+    CMP_REQUIRE(grad_layers[i] && ((uintptr_t)grad_layers[i] % (uintptr_t)galign) == 0,
+                "grad_layers[%d] must be %d-byte aligned", i, galign);
     CMP_REQUIRE(grad_pitch_layers[i] >= in[i].roi.w, "grad_pitch_layers[%d] < roi.w", i);
   }
+  const bool work = !rect_empty(viewport) && n > 0;
+  if (work) {
+    CMP_REQUIRE(grad_out && ((uintptr_t)grad_out & 15) == 0, "grad_out must be 16-byte aligned");
+    CMP_REQUIRE(grad_pitch >= viewport.w, "grad_pitch < viewport.w");
+  }
+  const int tile_w = 64, tile_h = 4;
+  const int64_t tiles_x = (viewport.w + tile_w - 1) / tile_w;
+  const int64_t tiles = tiles_x * ((viewport.h + tile_h - 1) / tile_h);
+  CMP_REQUIRE(tiles < (1ll << 24), "too many tiles");
   hipStream_t s = (hipStream_t)stream;
   // zero the parts of the layer gradients that the viewport does not reach
+  ZeroArgs z;
+  int nz = 0, rows = 0;
+  auto zero = [&]() -> cmp_status {
+    const unsigned bx = (unsigned)std::min(64, (rows + kThreads / kWave - 1) / (kThreads / kWave));
+    if (grad_fmt == CMP_RGBA32F)
+      hipLaunchKernelGGL(zero_outside_kernel<f32x4>, dim3(bx, nz), dim3(kThreads), 0, s, z);
+    else
+      hipLaunchKernelGGL(zero_outside_kernel<f16x4>, dim3(bx, nz), dim3(kThreads), 0, s, z);
+    nz = rows = 0;
+    CMP_CHECK_HIP(hipGetLastError());
+    return CMP_OK;
+  };
   for (int i = 0; i < n; ++i) {
     const cmp_rect r = in[i].roi;
     if (rect_empty(r)) continue;
-    const bool inside = !rect_empty(viewport) && r.x >= viewport.x && r.y >= viewport.y &&
-                        (int64_t)r.x + r.w <= (int64_t)viewport.x + viewport.w &&
-                        (int64_t)r.y + r.h <= (int64_t)viewport.y + viewport.h;
-    if (inside) continue;
-    const int64_t npx = (int64_t)r.w * r.h;
-    const unsigned blocks = (unsigned)((npx + kThreads - 1) / kThreads < 4096
-                                           ? (npx + kThreads - 1) / kThreads
-                                           : 4096);
-    hipLaunchKernelGGL(zero_rgba_kernel, dim3(blocks), dim3(kThreads), 0, s, grad_layers[i],
-                       grad_pitch_layers[i], r.w, r.h);
-    CMP_CHECK_HIP(hipGetLastError());
+    auto cut = [](int64_t v, int64_t lo, int64_t hi) { return (int32_t)std::max(lo, std::min(v, hi)); };
+    ZeroLayer L{grad_layers[i], grad_pitch_layers[i], r.w, r.h, 0, 0, 0, 0};
+    if (!rect_empty(viewport)) {
+      L.ix0 = cut((int64_t)viewport.x - r.x, 0, r.w);
+      L.iy0 = cut((int64_t)viewport.y - r.y, 0, r.h);
+      L.ix1 = cut((int64_t)viewport.x + viewport.w - r.x, 0, r.w);
+      L.iy1 = cut((int64_t)viewport.y + viewport.h - r.y, 0, r.h);
+    }
+    if (L.ix0 == 0 && L.iy0 == 0 && L.ix1 == r.w && L.iy1 == r.h) continue;
+    if (L.ix1 <= L.ix0 || L.iy1 <= L.iy0) L.ix0 = L.iy0 = L.ix1 = L.iy1 = 0;
+    z.l[nz++] = L;
+    rows = std::max(rows, r.h);
+    if (nz == kBwdInline && (st = zero()) != CMP_OK) return st;
   }
-  if (rect_empty(viewport) || n == 0) return CMP_OK;
-  CMP_REQUIRE(grad_out && ((uintptr_t)grad_out & 15) == 0, "grad_out must be 16-byte aligned");
-  CMP_REQUIRE(grad_pitch >= viewport.w, "grad_pitch < viewport.w");
+  if (nz && (st = zero()) != CMP_OK) return st;
+  if (!work) return CMP_OK;
 
   BwdArgs a;
   memset(&a, 0, sizeof a);
@@ -478,23 +551,48 @@ extern "C" cmp_status cmp_composite_over_backward(const cmp_image* in, int32_t n
   a.vw = viewport.w;
   a.vh = viewport.h;
   a.n = n;
-  a.tile_w = 64;
-  a.tile_h = 4;
-  a.tiles_x = (viewport.w + a.tile_w - 1) / a.tile_w;
-  const int64_t tiles = (int64_t)a.tiles_x * ((viewport.h + a.tile_h - 1) / a.tile_h);
-  CMP_REQUIRE(tiles < (1ll << 24), "too many tiles");
+  a.tile_w = tile_w;
+  a.tile_h = tile_h;
+  a.tiles_x = (int32_t)tiles_x;
   const dim3 grid((unsigned)tiles), block(kThreads);
-  if (n <= kBwdInline) {
-    if (fmt == CMP_RGBA32F)
-      hipLaunchKernelGGL((over_bwd_kernel<CMP_RGBA32F, true>), grid, block, 0, s, a);
-    else
-      hipLaunchKernelGGL((over_bwd_kernel<CMP_RGBA16F, true>), grid, block, 0, s, a);
-  } else {
-    if (fmt == CMP_RGBA32F)
-      hipLaunchKernelGGL((over_bwd_kernel<CMP_RGBA32F, false>), grid, block, 0, s, a);
-    else
-      hipLaunchKernelGGL((over_bwd_kernel<CMP_RGBA16F, false>), grid, block, 0, s, a);
-  }
+  const bool f32 = fmt == CMP_RGBA32F, g32 = grad_fmt == CMP_RGBA32F;
+#define CMP_BWD_LAUNCH(F, GF)                                                             \
+  do {                                                                                    \
+    if (n <= kBwdInline)                                                                  \
+      hipLaunchKernelGGL((over_bwd_kernel<F, GF, true>), grid, block, 0, s, a);           \
+    else                                                                                  \
+      hipLaunchKernelGGL((over_bwd_kernel<F, GF, false>), grid, block, 0, s, a);          \
+  } while (0)
+  if (f32 && g32) CMP_BWD_LAUNCH(CMP_RGBA32F, CMP_RGBA32F);
+  else if (f32) CMP_BWD_LAUNCH(CMP_RGBA32F, CMP_RGBA16F);
+  else if (g32) CMP_BWD_LAUNCH(CMP_RGBA16F, CMP_RGBA32F);
+  else CMP_BWD_LAUNCH(CMP_RGBA16F, CMP_RGBA16F);
+#undef CMP_BWD_LAUNCH
   CMP_CHECK_HIP(hipGetLastError());
   return CMP_OK;
+}
+
+extern "C" cmp_status cmp_composite_over_backward(const cmp_image* in, int32_t n, cmp_format fmt,
+                                                  const int32_t* order_b2f, cmp_rect viewport,
+                                                  const float* grad_out, int64_t grad_pitch,
+                                                  float* const* grad_layers,
+                                                  const int64_t* grad_pitch_layers, void* workspace,
+                                                  size_t ws_bytes, void* stream) {
+  CMP_RANGE("cmp_composite_over_backward");
+  return over_backward_impl(in, n, fmt, order_b2f, viewport, grad_out, grad_pitch,
+                            (void* const*)grad_layers, CMP_RGBA32F, grad_pitch_layers, workspace,
+                            ws_bytes, stream);
+}
+
+extern "C" cmp_status cmp_composite_over_backward_as(const cmp_image* in, int32_t n,
+                                                     cmp_format fmt, const int32_t* order_b2f,
+                                                     cmp_rect viewport, const float* grad_out,
+                                                     int64_t grad_pitch, void* const* grad_layers,
+                                                     cmp_format grad_fmt,
+                                                     const int64_t* grad_pitch_layers,
+                                                     void* workspace, size_t ws_bytes,
+                                                     void* stream) {
+  CMP_RANGE("cmp_composite_over_backward_as");
+  return over_backward_impl(in, n, fmt, order_b2f, viewport, grad_out, grad_pitch, grad_layers,
+                            grad_fmt, grad_pitch_layers, workspace, ws_bytes, stream);
 }

@@ -38,13 +38,6 @@ struct RawPx { typedef f32x4 type; };
 template <>
 struct RawPx<CMP_RGBA16F> { typedef f16x4 type; };
 
-template <int FMT>
-__device__ __forceinline__ typename RawPx<FMT>::type ld_raw(const void* base, int64_t px) {
-  typedef const __attribute__((address_space(1))) typename RawPx<FMT>::type* GPtr;
-  // non-temporal: each layer pixel is read once (measured faster than the
-  // default policy for this kernel and the backward pass)
-  return __builtin_nontemporal_load(&((GPtr)base)[px]);
-}
 __device__ __forceinline__ f32x4 widen(f32x4 v) { return v; }
 __device__ __forceinline__ f32x4 widen(f16x4 h) {
   return f32x4{(float)h.x, (float)h.y, (float)h.z, (float)h.w};
@@ -63,15 +56,21 @@ __device__ __forceinline__ f32x4 over_op(f32x4 front, f32x4 back) {
                __builtin_fmaf(t, back.z, front.z), __builtin_fmaf(t, back.w, front.w)};
 }
 
-__device__ __forceinline__ bool tile_misses(int rx, int ry, int rw, int rh, int x0, int y0,
-                                            int tw, int th) {
-  return rw <= 0 || rh <= 0 || rx >= x0 + tw || rx + rw <= x0 || ry >= y0 + th || ry + rh <= y0;
-}
-
 // Up to 64 layers of a back-to-front list, one per lane.
 __device__ __forceinline__ OverDesc lane_layer(const OverDesc* __restrict__ d, int c0, int n) {
   const int j = c0 + (int)(threadIdx.x % kWave);
   return j < n ? d[j] : OverDesc{nullptr, 0, 0, 0, 0, 0};
+}
+
+// The address of pixel (X0, Y) of a layer placed at (x, y).
+template <int FMT>
+__device__ __forceinline__ uint64_t over_address(const void* base, int64_t pitch, int32_t x,
+                                                 int32_t y, int X0, int Y) {
+  constexpr int bpp = FMT == CMP_RGBA32F ? 16 : 8;
+  const int dx = __builtin_elementwise_sub_sat(x, X0);   // exact where the layer reaches the segment
+  const uint32_t dy = (uint32_t)Y - (uint32_t)y;
+  return (uint64_t)reinterpret_cast<uintptr_t>(base) +
+         ((uint64_t)dy * (uint64_t)pitch - (uint64_t)(int64_t)dx) * bpp;
 }
 
 // This lane's layer at the row segment [X0, X0 + cols) of row Y (cols <= 64):
@@ -86,15 +85,13 @@ struct OverSeg {
 template <int FMT>
 __device__ __forceinline__ OverSeg over_segment(const OverDesc& D, int X0, int cols, int Y,
                                                 uint64_t& hits) {
-  constexpr int bpp = FMT == CMP_RGBA32F ? 16 : 8;
   // saturating, so that placements near the ends of the 32-bit range work
   // too: where a layer reaches the segment nothing saturates
   const int dx = __builtin_elementwise_sub_sat(D.x, X0);
   const uint32_t dy = (uint32_t)Y - (uint32_t)D.y;
   const int first = min(max(dx, 0), kWave), end = min(__builtin_elementwise_add_sat(dx, D.w), cols);
   hits = (uint64_t)__ballot(dy < (uint32_t)D.h && first < end);
-  const uint64_t a = (uint64_t)reinterpret_cast<uintptr_t>(D.color) +
-                     ((uint64_t)dy * (uint64_t)D.pitch - (uint64_t)(int64_t)dx) * bpp;
+  const uint64_t a = over_address<FMT>(D.color, D.pitch, D.x, D.y, X0, Y);
   return OverSeg{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)first | (uint32_t)(end - first) << 8};
 }
 
