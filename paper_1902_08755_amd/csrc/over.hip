@@ -25,11 +25,19 @@ struct OverArgs {
 };
 static_assert(sizeof(OverArgs) <= 4096, "kernel arguments must fit in 4 KiB");
 
+// Consecutive tiles per XCD: neighbouring tiles share the cache lines of rows
+// that are no multiple of 128 bytes, and one L2 then reads them once (20 FP32
+// layers of 1919x1079: 127 us in launch order, 120 in runs of 16; 40 FP16 of
+// 1921x1081: 143, 130.6; in 8 binary-swap groups 160, 150; 32 FP32 of
+// 1024x1024: 100.5, 92; 16 of 3840x2160, whose lines nothing shares: 376
+// either way). Runs of 256 spread 1024x1024 better over the memory channels
+// (88 us) and lose on the others (122 us, 130.6, 378).
+constexpr int kFwdRun = 16;
+
 __device__ __forceinline__ void region_tile(const Region* reg, int nreg, int tile_w, int tile_h,
                                             int& x0, int& y0, int& tw, int& th) {
-  const int blk = blockIdx.x;
-  int r = 0;
-  r = segment_of([&](int i) { return reg[i].tile_begin; }, nreg, blk);
+  const int blk = xcd_tile((int)blockIdx.x, (int)gridDim.x, kFwdRun);
+  const int r = segment_of([&](int i) { return reg[i].tile_begin; }, nreg, blk);
   const Region R = reg[r];
   const int local = blk - R.tile_begin;
   const int tiles_x = (R.w + tile_w - 1) / tile_w;
