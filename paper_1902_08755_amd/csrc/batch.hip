@@ -35,6 +35,8 @@ cmp_status validate_depth_inputs(const cmp_image* in, int32_t n);
 cmp_status validate_over_inputs(const cmp_image* in, int32_t n, cmp_format fmt,
                                 const int32_t* order);
 
+constexpr int kPlaceMax = 64;   // contributors of a depth job staged in LDS at a time
+
 struct JobRec {
   int32_t kind, fmt, n, desc_off;
   int32_t vx, vy, vw, vh;
@@ -83,7 +85,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))
       for (int c0 = 0; c0 < jn || c0 == 0; c0 += kPlaceMax) {
         const int cn = min(kPlaceMax, jn - c0);
         if (c0 > 0) __syncthreads();   // the previous chunk's records are no longer read
-        stage_contributors(DepthSrc{a.ddesc + J.desc_off + c0, nullptr, 0, 0}, cn, s_rec);
+        const DepthDesc* dd = a.ddesc + J.desc_off + c0;
+        stage_contributors([&](int i) { return dd[i]; }, cn, nullptr, 0, 0, s_rec);
         for (int tile = uniform(I.tile0); tile < t1; ++tile) {
           const int ty = tile / J.tiles_x, tx = tile - ty * J.tiles_x;
           const int x0 = J.vx + tx * J.tile_w, y0 = J.vy + ty * J.tile_h;

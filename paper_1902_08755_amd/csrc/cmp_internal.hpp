@@ -103,15 +103,6 @@ __device__ __forceinline__ int wave_max(int v) {
 }
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int64_t uniform64(int64_t v) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-template <typename T>
-__device__ __forceinline__ T* uniform_ptr(T* p) {
-  return reinterpret_cast<T*>(uniform64((int64_t)reinterpret_cast<uintptr_t>(p)));
-}
 
 // The segment holding workgroup blk: the last i < n whose first workgroup
 // begin_of(i) is <= blk (begin_of(0) == 0, ascending). Every begin_of(i) is
@@ -146,22 +137,6 @@ __device__ __forceinline__ void wave_lds_fence() {
 __device__ __forceinline__ int xcd_tile(int blk, int total, int chunk) {
   const int group = 8 * chunk, base = blk / group * group, r = blk - base;
   return base + group <= total ? base + (r % 8) * chunk + r / 8 : blk;
-}
-
-// The placement of contributor i: the host rectangle, or the device one
-// (clamped to the host rectangle's size, which bounds the buffer).
-__device__ __forceinline__ void placement(const int32_t* roi_dev, int idx, int32_t hx, int32_t hy,
-                                          int32_t hw, int32_t hh, int32_t& x, int32_t& y,
-                                          int32_t& w, int32_t& h) {
-  if (roi_dev) {
-    const int4 r = reinterpret_cast<const int4*>(roi_dev)[idx];
-    x = uniform(r.x);
-    y = uniform(r.y);
-    w = uniform(max(0, min(r.z, hw)));
-    h = uniform(max(0, min(r.w, hh)));
-  } else {
-    x = hx; y = hy; w = hw; h = hh;
-  }
 }
 
 }  // namespace cmp

@@ -7,12 +7,20 @@
 
 namespace cmp {
 
-constexpr int kDepthPerPass = 48;
-static_assert(kDepthPerPass <= kPlaceMax, "placements of a pass are staged in LDS");
+// A pass's contributors and regions share the words of the kernel's arguments:
+// kDescWords per contributor from the front, kRegionWords per region from the
+// back. Up to 111 contributors fit (direct send to 16 owners: 102), so few
+// calls need a second pass over the outputs (100 contributors over 1920x1080
+// took three passes of 48, 22 + 22 + 11 us; one pass takes 30.7, 200 over
+// 1281x719 five passes, 59 us, and now two, 37).
+// A pitch is one word; where one does not fit, the upper words of all of them
+// follow the contributors.
+constexpr int kArgWords = 1004;
+constexpr int kDescWords = 9, kRegionWords = sizeof(Region) / 4;
+constexpr int kDepthPerPass = (kArgWords - kRegionWords) / kDescWords;
+constexpr int kColorOnly = 48;   // most contributors without a depth output (include/cmp.h)
 
 struct DepthArgs {
-  DepthDesc c[kDepthPerPass];
-  Region reg[kMaxRegions];
   const int32_t* roi_dev;
   uint32_t* out_color;
   uint32_t* out_depth;
@@ -23,15 +31,30 @@ struct DepthArgs {
   int32_t accumulate;
   int32_t index_base;
   int32_t crop;   // roi_dev crops the placed contributors (else it places them)
+  int32_t wide;   // pitches have upper words
+  uint32_t words[kArgWords];
 };
 static_assert(sizeof(DepthArgs) <= 4096, "kernel arguments must fit in 4 KiB");
+static_assert(kColorOnly <= (kArgWords - kMaxRegions * kRegionWords) / (kDescWords + 1),
+              "one pass takes kColorOnly contributors whatever the regions and pitches");
+
+// Consecutive tiles per XCD: neighbouring tiles share the cache lines of rows
+// that are no multiple of 128 bytes, and one L2 then reads them once (40
+// partial contributors of 1920x1080: 14.7 us in launch order, 12.7 in runs of
+// 16, 14.9 of 64; 30 of 1367x763: 25.9, 21.2, 22.0; 8 of 3841x2161: 61.1,
+// 56.0, 56.1; 64 of 3840x2160 for 64 owners: 169, 167, 188).
+constexpr int kDepthRun = 16;
 
 __device__ __forceinline__ void tile_of_block(const Region* reg, int nreg, int tile_w, int tile_h,
                                               int& x0, int& y0, int& tw, int& th) {
-  const int blk = blockIdx.x;
-  int r = 0;
-  r = segment_of([&](int i) { return reg[i].tile_begin; }, nreg, blk);
-  const Region R = reg[r];
+  const int blk = xcd_tile((int)blockIdx.x, (int)gridDim.x, kDepthRun);
+  // lane i holds region i (nreg <= 64, ascending tile_begin from 0)
+  const int lane = threadIdx.x % kWave;
+  const Region mine = reg[min(lane, nreg - 1)];
+  const int r = (int)__builtin_popcountll(__ballot(lane < nreg && mine.tile_begin <= blk)) - 1;
+  auto of_lane = [r](int v) { return __builtin_amdgcn_readlane(v, r); };
+  const Region R{of_lane(mine.x), of_lane(mine.y), of_lane(mine.w), of_lane(mine.h),
+                 of_lane(mine.tile_begin)};
   const int local = blk - R.tile_begin;
   const int tiles_x = (R.w + tile_w - 1) / tile_w;
   const int ty = local / tiles_x, tx = local - ty * tiles_x;
@@ -48,10 +71,20 @@ __device__ __forceinline__ void tile_of_block(const Region* reg, int nreg, int t
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void depth_kernel(
     const DepthArgs a) {
   int x0, y0, tw, th;
-  tile_of_block(a.reg, a.nreg, a.tile_w, a.tile_h, x0, y0, tw, th);
-  const DepthSrc src{a.c, a.roi_dev, a.index_base, a.crop};
-  __shared__ DepthRec s_rec[kPlaceMax];
-  stage_contributors(src, a.n, s_rec);   // a.n <= kDepthPerPass <= kPlaceMax
+  tile_of_block(reinterpret_cast<const Region*>(a.words + kArgWords) - a.nreg, a.nreg, a.tile_w,
+                a.tile_h, x0, y0, tw, th);
+  __shared__ DepthRec s_rec[kDepthPerPass];
+  stage_contributors(
+      [&](int i) {
+        const uint32_t* d = a.words + kDescWords * i;
+        auto ptr = [&](int k) {
+          return reinterpret_cast<const uint32_t*>((uint64_t)d[k + 1] << 32 | d[k]);
+        };
+        const uint32_t up = a.wide ? a.words[kDescWords * a.n + i] : 0u;
+        return DepthDesc{ptr(0), ptr(2), (int64_t)((uint64_t)up << 32 | d[4]), (int32_t)d[5],
+                         (int32_t)d[6], (int32_t)d[7], (int32_t)d[8]};
+      },
+      a.n, a.roi_dev, a.index_base, a.crop, s_rec);   // a.n <= kDepthPerPass
   depth_tile(s_rec, a.n, x0, y0, tw, th, a.out_color, a.out_depth, a.out_pitch, a.vx, a.vy,
              a.accumulate != 0);
 }
@@ -90,9 +123,9 @@ static cmp_status composite_depth_impl(const cmp_image* in, int32_t n, const int
               viewport.w);
   CMP_REQUIRE(((uintptr_t)out_color & 3) == 0 && ((uintptr_t)out_depth & 3) == 0,
               "outputs must be 4-byte aligned");
-  CMP_REQUIRE(n <= kDepthPerPass || out_depth,
+  CMP_REQUIRE(n <= kColorOnly || out_depth,
               "out_depth is required when n > %d (it carries the result between passes)",
-              kDepthPerPass);
+              kColorOnly);
   CMP_REQUIRE(((uintptr_t)roi_dev & 15) == 0, "roi_dev must be 16-byte aligned");
   const int tw = tile.w ? tile.w : 64, th = tile.h ? tile.h : 16;
   CMP_REQUIRE(tw > 0 && th > 0 && (int64_t)tw * th <= 65536,
@@ -101,8 +134,10 @@ static cmp_status composite_depth_impl(const cmp_image* in, int32_t n, const int
   DepthArgs a;
   memset(&a, 0, sizeof a);
   int64_t tiles = 0;
-  const int nreg = plan_regions(sched, viewport, tw, th, a.reg, &tiles);
+  Region reg[kMaxRegions];
+  const int nreg = plan_regions(sched, viewport, tw, th, reg, &tiles);
   if (nreg < 0) return nreg;
+  memcpy(a.words + kArgWords - nreg * kRegionWords, reg, nreg * sizeof(Region));
   CMP_REQUIRE(tiles < (1ll << 24), "too many tiles (%lld)", (long long)tiles);
   a.roi_dev = roi_dev;
   a.crop = crop ? 1 : 0;
@@ -115,14 +150,31 @@ static cmp_status composite_depth_impl(const cmp_image* in, int32_t n, const int
   a.tile_w = tw;
   a.tile_h = th;
   hipStream_t s = (hipStream_t)stream;
+  bool wide = false;
+  for (int i = 0; i < n; ++i)
+    if (!rect_empty(in[i].roi) && in[i].pitch > (int64_t)UINT32_MAX) wide = true;
+  a.wide = wide ? 1 : 0;
+  const int most = (kArgWords - nreg * kRegionWords) / (kDescWords + a.wide);
   int base = 0;
   do {
-    const int cnt = n - base < kDepthPerPass ? n - base : kDepthPerPass;
+    const int cnt = n - base < most ? n - base : most;
     for (int i = 0; i < cnt; ++i) {
       const cmp_image& I = in[base + i];
-      a.c[i] = DepthDesc{I.depth ? (const uint32_t*)I.color : nullptr, I.depth, I.pitch,
-                         I.roi.x, I.roi.y, rect_empty(I.roi) ? 0 : I.roi.w,
-                         rect_empty(I.roi) ? 0 : I.roi.h};
+      const bool empty = rect_empty(I.roi);
+      const uint64_t v[3] = {empty ? 0 : (uint64_t)(uintptr_t)I.color,
+                             empty ? 0 : (uint64_t)(uintptr_t)I.depth,
+                             empty ? 0 : (uint64_t)I.pitch};
+      uint32_t* d = a.words + kDescWords * i;
+      for (int k = 0; k < 2; ++k) {
+        d[2 * k] = (uint32_t)v[k];
+        d[2 * k + 1] = (uint32_t)(v[k] >> 32);
+      }
+      d[4] = (uint32_t)v[2];
+      d[5] = (uint32_t)I.roi.x;
+      d[6] = (uint32_t)I.roi.y;
+      d[7] = empty ? 0 : (uint32_t)I.roi.w;
+      d[8] = empty ? 0 : (uint32_t)I.roi.h;
+      if (wide) a.words[kDescWords * cnt + i] = (uint32_t)(v[2] >> 32);
     }
     a.n = cnt;
     a.accumulate = base > 0;

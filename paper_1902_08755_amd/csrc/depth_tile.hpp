@@ -28,23 +28,12 @@ struct DepthDesc {
   int32_t x, y, w, h;   // placement (host rectangle; bounds the buffer)
 };
 
-// Source of contributor descriptors; `roi_dev` may override placements
-// (crop == 0) or crop the contributors to the rectangles that hold their
-// data (crop == 1: the buffers stay where the descriptors place them).
-struct DepthSrc {
-  const DepthDesc* d;
-  const int32_t* roi_dev;   // device int32[n][4] or nullptr
-  int index_base;           // row of roi_dev that corresponds to d[0]
-  int crop;
-};
-
 // Composites the tile [x0, x0+tw) x [y0, y0+th) (destination pixels) of a
 // viewport whose origin is (vx, vy) into out_color/out_depth. With
 // `accumulate`, the outputs already hold the result of earlier contributors
 // (a previous pass) and are combined under the same rule.
 constexpr int kDepthRows = 4;    // rows per lane per step
 constexpr int kDepthBatch = 4;   // covering contributors whose loads are in flight together
-constexpr int kPlaceMax = 64;    // contributors staged in LDS per call
 
 typedef const __attribute__((address_space(1))) uint32_t* GlobalU32;
 
@@ -56,16 +45,22 @@ struct DepthRec {
   int64_t pitch;
 };
 
-// Stages contributors [0, n) (n <= kPlaceMax) in LDS: their placements (the
-// host rectangle or the device ROI, clamped to the host size) and buffers.
-// All threads of the workgroup; ends with a barrier.
-__device__ __forceinline__ void stage_contributors(const DepthSrc& src, int n, DepthRec* rec) {
+// Stages contributors [0, n) in LDS: their placements (the host rectangle or
+// the device ROI, clamped to the host size) and buffers. desc(i) gives
+// contributor i's descriptor. `roi_dev` (device int32[][4], row index_base + i
+// for contributor i) may override placements (crop == 0) or crop the
+// contributors to the rectangles that hold their data (crop == 1: the buffers
+// stay where the descriptors place them). All threads of the workgroup; ends
+// with a barrier.
+template <typename F>
+__device__ __forceinline__ void stage_contributors(F desc, int n, const int32_t* roi_dev,
+                                                   int index_base, int crop, DepthRec* rec) {
   for (int i = threadIdx.x; i < n; i += kThreads) {
-    const DepthDesc& D = src.d[i];
+    const DepthDesc D = desc(i);
     DepthRec r{D.x, D.y, D.w, D.h, D.depth, D.color, D.pitch};
-    if (src.roi_dev && src.crop) {
+    if (roi_dev && crop) {
       // the part of the placed buffer inside the device rectangle
-      const int4 q = reinterpret_cast<const int4*>(src.roi_dev)[src.index_base + i];
+      const int4 q = reinterpret_cast<const int4*>(roi_dev)[index_base + i];
       const int x0 = max(q.x, D.x), y0 = max(q.y, D.y);
       const int x1 = min(q.x + max(q.z, 0), D.x + D.w), y1 = min(q.y + max(q.w, 0), D.y + D.h);
       r.x = x0;
@@ -77,8 +72,8 @@ __device__ __forceinline__ void stage_contributors(const DepthSrc& src, int n, D
         r.depth = D.depth + o;
         r.color = D.color + o;
       }
-    } else if (src.roi_dev) {
-      const int4 q = reinterpret_cast<const int4*>(src.roi_dev)[src.index_base + i];
+    } else if (roi_dev) {
+      const int4 q = reinterpret_cast<const int4*>(roi_dev)[index_base + i];
       r.x = q.x;
       r.y = q.y;
       r.w = max(0, min(q.z, D.w));
@@ -90,36 +85,31 @@ __device__ __forceinline__ void stage_contributors(const DepthSrc& src, int n, D
   __syncthreads();
 }
 
-// `rec`: contributors staged by stage_contributors (n <= kPlaceMax).
-// Per step a wave first finds which contributors cover its rows and the
-// tile's columns: lane i tests contributor i and one ballot gives the 64-bit
-// mask (a loop over the contributors with uniform compares took a quarter of
-// the kernel's vector instructions). It then loads kDepthBatch covering
-// contributors x 4 rows at a time, so the depth loads of a typical step are
-// one round trip; the winner's colour is gathered at the end.
+// `rec`: contributors staged by stage_contributors.
+// Per step a wave takes 64 contributors at a time, one per lane: whether the
+// contributor covers pixels of the wave's rows and columns, the address of the
+// step's first pixel in it, its row pitch, and the columns and rows it covers.
+// A ballot lists the covering ones; each of them then costs five lane reads
+// and scalar arithmetic for its row addresses (it replaces LDS reads made
+// uniform and tests of row and column per lane: 40 partial contributors over
+// 1920x1080 15.3 -> 14.7 us, 200 over 1281x719 68.7 -> 65.3).
+// kDepthBatch covering contributors x 4 rows are loaded at a time, so the
+// depth loads of a typical step are one round trip; the winner's colour is
+// gathered at the end.
 __device__ __forceinline__ void depth_tile(const DepthRec* rec, int n, int x0, int y0, int tw,
                                            int th, uint32_t* __restrict__ out_color,
                                            uint32_t* __restrict__ out_depth, int64_t out_pitch,
                                            int vx, int vy, bool accumulate) {
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  typedef const __attribute__((address_space(1))) char* Bytes;
+  const int lane = threadIdx.x % kWave, wave = uniform((int)(threadIdx.x / kWave));
   constexpr int kStepRows = kDepthRows * (kThreads / kWave);
   for (int cx = 0; cx < tw; cx += kWave) {
-    const int X = x0 + cx + lane;
-    const bool col_ok = cx + lane < tw;
-    const int cx0 = x0 + cx, cx1 = x0 + min(tw, cx + kWave);   // the wave's columns
+    const int cx0 = x0 + cx, cols = min(kWave, tw - cx);   // the wave's columns
+    const int X = cx0 + lane;
+    const bool col_ok = lane < cols;
     for (int r0 = wave * kDepthRows; r0 < th; r0 += kStepRows) {
       const int Y0 = y0 + r0;                       // rows Y0 .. Y0 + 3 (uniform)
       const int nrows = min(kDepthRows, th - r0);
-      // covering contributors of this step: lane i tests contributor i
-      // (n <= 64), one ballot gives the mask (bit i: contributor i). Every
-      // lane of the wave is active here: the loops above are uniform over
-      // the wave and callers run depth_tile with the whole workgroup.
-      bool covers_i = false;
-      if (lane < n) {
-        const DepthRec& R = rec[lane];
-        covers_i = R.w > 0 && R.x < cx1 && R.x + R.w > cx0 && R.y < Y0 + nrows && R.y + R.h > Y0;
-      }
-      uint64_t cover = (uint64_t)__ballot(covers_i);
       uint32_t bd[kDepthRows], pc[kDepthRows];
       int bi[kDepthRows];
 #pragma unroll
@@ -133,54 +123,65 @@ __device__ __forceinline__ void depth_tile(const DepthRec* rec, int n, int x0, i
           pc[k] = out_color[oo];
         }
       }
-      while (cover) {   // uniform
-        // the next kDepthBatch covering contributors (a slot past the last
-        // one repeats the first and is ignored), then every load of the
-        // batch, then the compares: no branch between the loads
-        int ids[kDepthBatch];
-        bool has[kDepthBatch];
-        const int first = (int)__builtin_ctzll(cover);
+      for (int c0 = 0; c0 < n; c0 += kWave) {   // uniform
+        // lane i: contributor c0 + i (every lane of the wave is active: the
+        // loops are uniform over it). Saturating, so that placements near the
+        // ends of the 32-bit range work too: where a contributor covers
+        // pixels of the step nothing saturates.
+        const DepthRec& R = rec[min(c0 + lane, n - 1)];
+        const int dx = __builtin_elementwise_sub_sat(R.x, cx0);
+        const int dy = __builtin_elementwise_sub_sat(R.y, Y0);
+        const int first = min(max(dx, 0), kWave), end = min(__builtin_elementwise_add_sat(dx, R.w), cols);
+        const int k0 = min(max(dy, 0), kDepthRows), k1 = min(__builtin_elementwise_add_sat(dy, R.h), nrows);
+        uint64_t cover = (uint64_t)__ballot(c0 + lane < n && first < end && k0 < k1);
+        const uint64_t pb = (uint64_t)R.pitch * 4;
+        // of row Y0 + k0, the first covered one
+        const uint64_t ad = (uint64_t)reinterpret_cast<uintptr_t>(R.depth) +
+                            (uint64_t)(uint32_t)(k0 - dy) * pb - (uint64_t)((int64_t)dx * 4);
+        const uint32_t span = (uint32_t)first | (uint32_t)(end - first) << 8 | (uint32_t)k0 << 16 |
+                              (uint32_t)k1 << 20;
+        auto of_lane = [](uint32_t v, int i) {
+          return (uint32_t)__builtin_amdgcn_readlane((int)v, i);
+        };
+        while (cover) {   // uniform
+          // the next kDepthBatch covering contributors (a slot past the last
+          // one repeats the first and is ignored), then every load of the
+          // batch, then the compares: no branch between the loads
+          int ids[kDepthBatch];
+          uint32_t dv[kDepthBatch][kDepthRows];
+          bool ok[kDepthBatch][kDepthRows];
+          const int i0 = (int)__builtin_ctzll(cover);
 #pragma unroll
-        for (int j = 0; j < kDepthBatch; ++j) {
-          has[j] = cover != 0;
-          ids[j] = has[j] ? (int)__builtin_ctzll(cover) : first;
-          cover &= cover - 1;
-        }
-        uint32_t dv[kDepthBatch][kDepthRows];
-        bool ok[kDepthBatch][kDepthRows];
+          for (int j = 0; j < kDepthBatch; ++j) {
+            const bool has = cover != 0;
+            const int i = has ? (int)__builtin_ctzll(cover) : i0;
+            cover &= cover - 1;
+            ids[j] = c0 + i;
+            const uint32_t s = of_lane(span, i);
+            const uint64_t pitch = (uint64_t)of_lane((uint32_t)(pb >> 32), i) << 32 | of_lane((uint32_t)pb, i);
+            uint64_t row = (uint64_t)of_lane((uint32_t)(ad >> 32), i) << 32 | of_lane((uint32_t)ad, i);
+            const uint32_t f = s & 0xFFu, cnt = has ? (s >> 8) & 0xFFu : 0u;
+            const int a0 = (int)(s >> 16) & 15, a1 = (int)(s >> 20);
+            // a pixel outside the contributor reads its first covered column
+            // or a covered row instead
+            const bool in_col = (uint32_t)lane - f < cnt;
+            const uint32_t off = (in_col ? (uint32_t)lane : f) * 4u;
 #pragma unroll
-        for (int j = 0; j < kDepthBatch; ++j) {
-          const int i = ids[j];
-          // the column test is per lane anyway: x and w stay in vector registers
-          const int rx = rec[i].x, ry = uniform(rec[i].y);
-          const int rw = rec[i].w, rh = uniform(rec[i].h);
-          // global (not flat) loads: flat ones would also hold up the LDS counter
-          const GlobalU32 dep = (GlobalU32)uniform_ptr(rec[i].depth);
-          const int64_t pitch = uniform64(rec[i].pitch);
-          const bool in_col = has[j] && col_ok && X >= rx && X < rx + rw;
-          const int lo = in_col ? X - rx : 0;   // this lane's column in the contributor
-          // a uniform row offset (one multiply per contributor, then one
-          // pitch per row) plus the lane's column; a pixel outside the
-          // contributor reads the first pixel of a valid row instead
-          const int yy0 = Y0 - ry;               // uniform
-          int64_t roff = (int64_t)yy0 * pitch;
-#pragma unroll
-          for (int k = 0; k < kDepthRows; ++k) {
-            const int yy = yy0 + k;
-            const bool rok = k < nrows && yy >= 0 && yy < rh;
-            dv[j][k] = dep[(rok ? roff : 0) + lo];
-            ok[j][k] = rok && in_col;
-            roff += pitch;
+            for (int k = 0; k < kDepthRows; ++k) {
+              dv[j][k] = *(GlobalU32)((Bytes)row + off);
+              ok[j][k] = in_col && k >= a0 && k < a1;
+              if (k >= a0 && k + 1 < a1) row += pitch;
+            }
           }
-        }
-        // ascending indices and a strict "<": ties keep the lower index
+          // ascending indices and a strict "<": ties keep the lower index
 #pragma unroll
-        for (int j = 0; j < kDepthBatch; ++j) {
+          for (int j = 0; j < kDepthBatch; ++j) {
 #pragma unroll
-          for (int k = 0; k < kDepthRows; ++k) {
-            if (ok[j][k] && dv[j][k] < bd[k]) {
-              bd[k] = dv[j][k];
-              bi[k] = ids[j];
+            for (int k = 0; k < kDepthRows; ++k) {
+              if (ok[j][k] && dv[j][k] < bd[k]) {
+                bd[k] = dv[j][k];
+                bi[k] = ids[j];
+              }
             }
           }
         }
