@@ -1,16 +1,28 @@
 // Batched compositing: many uneven jobs in one persistent launch.
 //
 // The plan cuts every job into workgroup tiles, groups runs of consecutive
-// tiles into work items of about kItemBytes of traffic (so the shared queue
-// counter is touched rarely), orders the items largest first
-// (longest-processing-time order: big items start early, small ones fill the
-// tail) and uploads the job records,
-// contributor descriptors and items to the caller's workspace. The kernel's
-// workgroups, sized to fill the GPU once, pull items from an atomic queue
-// counter until it runs dry, like render clients pulling tile work packages
-// from a server-side queue (Section 4.2.4, Tiles; Section 6.2.1, Dynamic Work
-// Packages). A completion counter lets the last workgroup reset the queue, so
-// a captured graph can replay the launch without any reset node.
+// tiles into work items of about kItemBytes of traffic, orders the items
+// largest first (longest-processing-time order: big items start early, small
+// ones fill the tail) and uploads the job records, contributor descriptors
+// and items to the caller's workspace. The kernel's workgroups, sized to fill
+// the GPU once, pull items until there are none left, like render clients
+// pulling tile work packages from a server-side queue (Section 4.2.4, Tiles;
+// Section 6.2.1, Dynamic Work Packages).
+//
+// One counter serves a draw every 11 to 14 ns however many workgroups ask, so
+// a single queue bounds the batch where its items are small (60 jobs of up to
+// 1024x1024 in 16000 items: 223 us), and large items leave workgroups idle at
+// the end (items of 512 KB: 198 us). Hence one queue per XCD, each on a cache
+// line of its own: runs of kRun consecutive items belong to one queue, so that
+// the tiles which share cache lines meet in one L2; a workgroup's first item
+// is its own without a draw, the next is drawn while the current one is
+// composited, and a workgroup whose queue is empty takes from the others.
+// Items of 64 KB, 60 jobs: 109 us; 256 jobs of 64 to 2048 pixels a side, one
+// set of buffers: 1600 us (a single queue with items of 512 KB: 1841, of 128
+// KB: 1698; queues and items of 32 KB: 1638, of 128 KB: 1707; runs of 1, 16,
+// 64 items instead of 4: 1662, 1610, 1649). A completion counter lets the last
+// workgroup reset the queues, so a captured graph can replay the launch
+// without any reset node.
 //
 // Each item runs the same tile body as the plain launch, so a job's pixels
 // are bit-identical to cmp_composite_depth / cmp_composite_over (SEQ).
@@ -43,21 +55,59 @@ struct JobRec {
   void* out_color;
   uint32_t* out_depth;
   int64_t out_pitch;
-  int32_t tile_w, tile_h, tiles_x, pad;
+  int32_t tile_w, tile_h, tiles_x, ntiles;
+  int32_t per_item, pad;   // tiles of an item (the job's last one may have fewer)
 };
 
 struct Item {
-  int32_t job, tile0, ntiles, pad;   // tiles [tile0, tile0 + ntiles) of one job
+  int32_t job, tile0;   // up to per_item tiles of one job from tile0 on
 };
 
 struct BatchArgs {
-  uint32_t* ctl;            // [0] next item, [1] finished workgroups
+  uint32_t* ctl;            // kQueues draw counters, then the finished workgroups,
+                            // one every kCtlWords
   const JobRec* jobs;
   const DepthDesc* ddesc;
   const OverDesc* odesc;
   const Item* items;
   int32_t nitems;
 };
+
+constexpr int kQueues = 8;      // one per XCD
+constexpr int kCtlWords = 32;   // 128 bytes per counter
+constexpr int kRun = 4;         // consecutive items of one queue
+
+// Item k of queue q. Items past the last one may come up in any queue: every
+// caller compares with nitems.
+__device__ __forceinline__ int item_of(int q, int k) {
+  return (k / kRun * kQueues + q) * kRun + k % kRun;
+}
+// The items of queue q that its workgroups start with, one each.
+__device__ __forceinline__ int first_items(int q) {
+  return ((int)gridDim.x - q + kQueues - 1) / kQueues;
+}
+__device__ __forceinline__ int draw(uint32_t* c) {
+  return (int)__hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// An item of any queue, nitems if all are empty (item_of grows with k, so an
+// empty queue stays empty, and a failed draw means that another one emptied).
+// The queues after q come first, so that the workgroups of one XCD spread.
+__device__ __forceinline__ int steal(uint32_t* ctl, int nitems, int q) {
+  while (true) {
+    int c[kQueues], from = -1;
+#pragma unroll
+    for (int k = 0; k < kQueues; ++k)
+      c[k] = (int)__hip_atomic_load(ctl + k * kCtlWords, __ATOMIC_RELAXED,
+                                    __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int k = 0; k < kQueues; ++k)
+      if (item_of(k, first_items(k) + c[k]) < nitems && (from < 0 || (k > q && from < q))) from = k;
+    if (from < 0) return nitems;
+    const int it = item_of(from, first_items(from) + draw(ctl + from * kCtlWords));
+    if (it < nitems) return it;
+  }
+}
 
 // Built for at least six waves per SIMD, which it fits in 77 VGPRs without a
 // spill (at the compiler's default it took five waves and 3% longer; eight
@@ -67,16 +117,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))
   __shared__ int s_item;
   __shared__ DepthRec s_rec[kPlaceMax];   // contributors of the current depth job
   const int tid = threadIdx.x;
-  while (true) {
-    if (tid == 0)
-      s_item = (int)__hip_atomic_fetch_add(&a.ctl[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    const int it = uniform(s_item);
-    __syncthreads();
-    if (it >= a.nitems) break;
+  const int q = (int)blockIdx.x % kQueues;
+  int it = item_of(q, (int)blockIdx.x / kQueues);
+  while (it < a.nitems) {   // uniform
+    int drawn = 0;
+    if (tid == 0) drawn = draw(a.ctl + q * kCtlWords);
     const Item I = a.items[it];
     const JobRec& J = a.jobs[uniform(I.job)];
-    const int t1 = uniform(I.tile0) + uniform(I.ntiles);
+    const int t1 = min(uniform(I.tile0) + uniform(J.per_item), uniform(J.ntiles));
     if (J.kind == 0) {
       // contributors in chunks of kPlaceMax staged in LDS; later chunks
       // combine with the output of earlier ones (the planner requires a
@@ -95,31 +143,36 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))
                      J.vx, J.vy, c0 > 0);
         }
       }
-      continue;
-    }
-    const int on = uniform(J.n);
-    const OverDesc* od = a.odesc + J.desc_off;
-    const OverDesc mine = lane_layer(od, 0, on);
-    for (int tile = uniform(I.tile0); tile < t1; ++tile) {
-      const int ty = tile / J.tiles_x, tx = tile - ty * J.tiles_x;
-      const int x0 = J.vx + tx * J.tile_w, y0 = J.vy + ty * J.tile_h;
-      const int tw = min(J.tile_w, J.vx + J.vw - x0), th = min(J.tile_h, J.vy + J.vh - y0);
-      if (J.fmt == CMP_RGBA32F) {
-        over_tile_seq<CMP_RGBA32F>(od, mine, on, x0, y0, tw, th, (float*)J.out_color,
-                                   J.out_pitch, J.vx, J.vy, false);
-      } else {
-        over_tile_seq<CMP_RGBA16F>(od, mine, on, x0, y0, tw, th, (float*)J.out_color,
-                                   J.out_pitch, J.vx, J.vy, false);
+    } else {
+      const int on = uniform(J.n);
+      const OverDesc* od = a.odesc + J.desc_off;
+      const OverDesc mine = lane_layer(od, 0, on);
+      for (int tile = uniform(I.tile0); tile < t1; ++tile) {
+        const int ty = tile / J.tiles_x, tx = tile - ty * J.tiles_x;
+        const int x0 = J.vx + tx * J.tile_w, y0 = J.vy + ty * J.tile_h;
+        const int tw = min(J.tile_w, J.vx + J.vw - x0), th = min(J.tile_h, J.vy + J.vh - y0);
+        if (J.fmt == CMP_RGBA32F) {
+          over_tile_seq<CMP_RGBA32F>(od, mine, on, x0, y0, tw, th, (float*)J.out_color,
+                                     J.out_pitch, J.vx, J.vy, false);
+        } else {
+          over_tile_seq<CMP_RGBA16F>(od, mine, on, x0, y0, tw, th, (float*)J.out_color,
+                                     J.out_pitch, J.vx, J.vy, false);
+        }
       }
     }
+    if (tid == 0) {
+      const int next = item_of(q, first_items(q) + drawn);
+      s_item = next < a.nitems ? next : steal(a.ctl, a.nitems, q);
+    }
+    __syncthreads();   // also: a depth job's records are no longer read
+    it = uniform(s_item);
+    __syncthreads();
   }
   if (tid == 0) {
     // no fence: nothing but the counters is shared with the last workgroup
-    const uint32_t done =
-        __hip_atomic_fetch_add(&a.ctl[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (done == gridDim.x - 1) {
-      __hip_atomic_store(&a.ctl[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&a.ctl[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (draw(a.ctl + kQueues * kCtlWords) == (int)gridDim.x - 1) {
+      for (int k = 0; k <= kQueues; ++k)
+        __hip_atomic_store(&a.ctl[k * kCtlWords], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
@@ -132,8 +185,13 @@ static const TileShape kDepthTiles[] = {{64, 16}, {64, 32}, {64, 64}, {128, 16},
                                         {256, 16}};
 static const TileShape kOverTiles[] = {{64, 4}, {128, 2}, {256, 1}, {32, 8}, {64, 8},
                                        {16, 16}, {64, 16}, {128, 8}};
-static const TileShape kDepthDefault = {64, 16}, kOverDefault = {64, 8};
-constexpr double kItemBytes = 512.0 * 1024.0;   // target traffic of one work item
+// Without a tuned tile: over tiles of a wide view are single rows, whose
+// neighbours in the row share the fewest cache lines (256 jobs of 64 to 2048
+// pixels a side: 1600 us, with 128x4 for all of them 1680); in a narrow view
+// they would leave lanes idle (100 jobs of up to 256x256: 65 us, 128x4 58).
+static const TileShape kDepthDefault = {64, 16}, kOverDefault = {128, 4}, kOverWide = {256, 1};
+constexpr int kWideView = 512;                 // pixels
+constexpr double kItemBytes = 64.0 * 1024.0;   // target traffic of one work item
 
 static int ilog2(int64_t v) {
   int r = 0;
@@ -200,7 +258,8 @@ static TileShape pick_tile(const std::vector<TuneEntry>& cache, const cmp_job& j
   const TuneKey k = key_of(j);
   for (const TuneEntry& e : cache)
     if (e.key == k) return e.tile;
-  return j.kind == 0 ? kDepthDefault : kOverDefault;
+  if (j.kind == 0) return kDepthDefault;
+  return j.viewport.w >= kWideView ? kOverWide : kOverDefault;
 }
 
 static cmp_status plain_job(const cmp_job& j, TileShape t, hipStream_t s) {
@@ -266,11 +325,13 @@ extern "C" cmp_status cmp_batch_plan_create(const cmp_job* jobs, int32_t njobs,
   std::vector<JobRec> recs;
   std::vector<DepthDesc> dd;
   std::vector<OverDesc> od;
-  struct Cand {
-    Item it;
+  // a job's items but for the last one cost the same: sorted as one
+  struct Items {
+    int32_t job, tile0, per_item, count;
     int64_t cost;
   };
-  std::vector<Cand> cands;
+  std::vector<Items> groups;
+  int64_t nitems = 0;
   // estimated bytes per pixel of a job: every contributor's share of the
   // viewport it covers, plus the output
   auto px_bytes = [](const cmp_job& j) -> double {
@@ -324,33 +385,36 @@ extern "C" cmp_status cmp_batch_plan_create(const cmp_job* jobs, int32_t njobs,
         od.push_back(OverDesc{I.color, I.pitch, I.roi.x, I.roi.y, e ? 0 : I.roi.w, e ? 0 : I.roi.h});
       }
     }
-    recs.push_back(r);
-    // work items: runs of consecutive tiles worth about kItemBytes of traffic,
-    // so the shared queue counter is touched rarely
-    const int tiles_y = r.vh ? (r.vh + t.h - 1) / t.h : 0;
-    const int ntiles = tiles_y * r.tiles_x;
+    // work items: runs of consecutive tiles worth about kItemBytes of traffic
+    r.ntiles = (r.vh ? (r.vh + t.h - 1) / t.h : 0) * r.tiles_x;
     const double tile_bytes = px_bytes(j) * t.w * t.h;
-    const int per_item = std::max(1, (int)(kItemBytes / std::max(1.0, tile_bytes)));
-    for (int t0 = 0; t0 < ntiles; t0 += per_item) {
-      const int cnt = std::min(per_item, ntiles - t0);
-      cands.push_back(Cand{Item{i, t0, cnt, 0}, (int64_t)(cnt * tile_bytes)});
-    }
+    r.per_item = std::max(1, (int)(kItemBytes / std::max(1.0, tile_bytes)));
+    recs.push_back(r);
+    auto add = [&](int tile0, int tiles, int count) {
+      groups.push_back(Items{i, tile0, tiles, count, (int64_t)(tiles * tile_bytes)});
+      nitems += count;
+    };
+    const int full = r.ntiles / r.per_item, rest = r.ntiles - full * r.per_item;
+    if (full) add(0, r.per_item, full);
+    if (rest) add(full * r.per_item, rest, 1);
   }
-  std::stable_sort(cands.begin(), cands.end(),
-                   [](const Cand& x, const Cand& y) { return x.cost > y.cost; });
-  P->nitems = (int32_t)cands.size();
+  std::stable_sort(groups.begin(), groups.end(),
+                   [](const Items& x, const Items& y) { return x.cost > y.cost; });
+  P->nitems = (int32_t)nitems;
   // device table layout
-  P->off_jobs = 64;
+  P->off_jobs = (kQueues + 1) * kCtlWords * sizeof(uint32_t);
   P->off_ddesc = align_up(P->off_jobs + recs.size() * sizeof(JobRec), 64);
   P->off_odesc = align_up(P->off_ddesc + dd.size() * sizeof(DepthDesc), 64);
   P->off_items = align_up(P->off_odesc + od.size() * sizeof(OverDesc), 64);
-  const size_t total = align_up(P->off_items + cands.size() * sizeof(Item), 64);
+  const size_t total = align_up(P->off_items + nitems * sizeof(Item), 64);
   P->blob.assign(total, 0);
   if (!recs.empty()) memcpy(P->blob.data() + P->off_jobs, recs.data(), recs.size() * sizeof(JobRec));
   if (!dd.empty()) memcpy(P->blob.data() + P->off_ddesc, dd.data(), dd.size() * sizeof(DepthDesc));
   if (!od.empty()) memcpy(P->blob.data() + P->off_odesc, od.data(), od.size() * sizeof(OverDesc));
   Item* items = (Item*)(P->blob.data() + P->off_items);
-  for (size_t k = 0; k < cands.size(); ++k) items[k] = cands[k].it;
+  for (const Items& g : groups)
+    for (int k = 0; k < g.count; ++k)
+      *items++ = Item{g.job, g.tile0 + k * g.per_item};
   // one wave of resident workgroups
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
