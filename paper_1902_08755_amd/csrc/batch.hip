@@ -139,8 +139,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))
           const int ty = tile / J.tiles_x, tx = tile - ty * J.tiles_x;
           const int x0 = J.vx + tx * J.tile_w, y0 = J.vy + ty * J.tile_h;
           const int tw = min(J.tile_w, J.vx + J.vw - x0), th = min(J.tile_h, J.vy + J.vh - y0);
-          depth_tile(s_rec, cn, x0, y0, tw, th, (uint32_t*)J.out_color, J.out_depth, J.out_pitch,
-                     J.vx, J.vy, c0 > 0);
+          depth_tile<kDepthRows>(s_rec, cn, x0, y0, tw, th, (uint32_t*)J.out_color, J.out_depth,
+                                 J.out_pitch, J.vx, J.vy, c0 > 0);
         }
       }
     } else {

@@ -45,12 +45,11 @@ static_assert(kColorOnly <= (kArgWords - kMaxRegions * kRegionWords) / (kDescWor
 // 56.0, 56.1; 64 of 3840x2160 for 64 owners: 169, 167, 188).
 constexpr int kDepthRun = 16;
 
-__device__ __forceinline__ void tile_of_block(const Region* reg, int nreg, int tile_w, int tile_h,
+__device__ __forceinline__ void tile_of_block(const Region& mine, int nreg, int tile_w, int tile_h,
                                               int& x0, int& y0, int& tw, int& th) {
   const int blk = xcd_tile((int)blockIdx.x, (int)gridDim.x, kDepthRun);
   // lane i holds region i (nreg <= 64, ascending tile_begin from 0)
   const int lane = threadIdx.x % kWave;
-  const Region mine = reg[min(lane, nreg - 1)];
   const int r = (int)__builtin_popcountll(__ballot(lane < nreg && mine.tile_begin <= blk)) - 1;
   auto of_lane = [r](int v) { return __builtin_amdgcn_readlane(v, r); };
   const Region R{of_lane(mine.x), of_lane(mine.y), of_lane(mine.w), of_lane(mine.h),
@@ -64,15 +63,11 @@ __device__ __forceinline__ void tile_of_block(const Region* reg, int nreg, int t
   th = min(tile_h, R.y + R.h - y0);
 }
 
-// Eight waves per SIMD: at the compiler's default the kernel used 106 SGPRs,
-// which held it to seven (measured on 16 x 1920x1080 cropped frames:
-// 22.85 -> 21.7 us; forcing eight on the over and batch kernels made them
-// spill and run slower).
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void depth_kernel(
-    const DepthArgs a) {
-  int x0, y0, tw, th;
-  tile_of_block(reinterpret_cast<const Region*>(a.words + kArgWords) - a.nreg, a.nreg, a.tile_w,
-                a.tile_h, x0, y0, tw, th);
+template <int kRows>
+__device__ __forceinline__ void depth_body(const DepthArgs& a) {
+  // in flight while the contributors are staged
+  const Region mine = (reinterpret_cast<const Region*>(a.words + kArgWords) -
+                       a.nreg)[min((int)(threadIdx.x % kWave), a.nreg - 1)];
   __shared__ DepthRec s_rec[kDepthPerPass];
   stage_contributors(
       [&](int i) {
@@ -85,8 +80,33 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
                          (int32_t)d[6], (int32_t)d[7], (int32_t)d[8]};
       },
       a.n, a.roi_dev, a.index_base, a.crop, s_rec);   // a.n <= kDepthPerPass
-  depth_tile(s_rec, a.n, x0, y0, tw, th, a.out_color, a.out_depth, a.out_pitch, a.vx, a.vy,
-             a.accumulate != 0);
+  int x0, y0, tw, th;
+  tile_of_block(mine, a.nreg, a.tile_w, a.tile_h, x0, y0, tw, th);
+  depth_tile<kRows>(s_rec, a.n, x0, y0, tw, th, a.out_color, a.out_depth, a.out_pitch, a.vx, a.vy,
+                    a.accumulate != 0);
+}
+
+// Eight waves per SIMD: at the compiler's default the kernel used 106 SGPRs,
+// which held it to seven (measured on 16 x 1920x1080 cropped frames:
+// 22.85 -> 21.7 us; forcing eight on the over and batch kernels made them
+// spill and run slower).
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void depth_kernel(
+    const DepthArgs a) {
+  depth_body<kDepthRows>(a);
+}
+
+// Two rows per lane, for views that have few tiles: a wave's chain of loads
+// (arguments, placements, depths, the winners' colours) is what takes the
+// time there, and twice the waves of half the rows overlap more of it. Below
+// kSmallTiles tiles of 64x16 (six workgroups per CU): 30 contributors over
+// 1367x763, 1056 tiles, 20.9 -> 19.3 us, 200 over 1281x719 36 -> 31, the
+// cropped frames of 24 x 1279x719 14.2 -> 12.3; above: 40 over 1920x1080, 2040
+// tiles, 12.9 -> 14.6, 8 over 3841x2161 57 -> 59.4. One row per lane is slower
+// at every size (28.6, 41.6).
+constexpr int kSmallRows = 2, kSmallTiles = 1536;
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void
+depth_small_kernel(const DepthArgs a) {
+  depth_body<kSmallRows>(a);
 }
 
 // Host-side validation of one contributor list; shared with the batch planner.
@@ -127,7 +147,7 @@ static cmp_status composite_depth_impl(const cmp_image* in, int32_t n, const int
               "out_depth is required when n > %d (it carries the result between passes)",
               kColorOnly);
   CMP_REQUIRE(((uintptr_t)roi_dev & 15) == 0, "roi_dev must be 16-byte aligned");
-  const int tw = tile.w ? tile.w : 64, th = tile.h ? tile.h : 16;
+  int tw = tile.w ? tile.w : 64, th = tile.h ? tile.h : 16;
   CMP_REQUIRE(tw > 0 && th > 0 && (int64_t)tw * th <= 65536,
               "tile %dx%d: sizes must be positive, area <= 65536", tw, th);
 
@@ -135,8 +155,13 @@ static cmp_status composite_depth_impl(const cmp_image* in, int32_t n, const int
   memset(&a, 0, sizeof a);
   int64_t tiles = 0;
   Region reg[kMaxRegions];
-  const int nreg = plan_regions(sched, viewport, tw, th, reg, &tiles);
+  int nreg = plan_regions(sched, viewport, tw, th, reg, &tiles);
   if (nreg < 0) return nreg;
+  const bool small = tile.w == 0 && tile.h == 0 && tiles < kSmallTiles;
+  if (small) {
+    th = kSmallRows * (kThreads / kWave);
+    nreg = plan_regions(sched, viewport, tw, th, reg, &tiles);
+  }
   memcpy(a.words + kArgWords - nreg * kRegionWords, reg, nreg * sizeof(Region));
   CMP_REQUIRE(tiles < (1ll << 24), "too many tiles (%lld)", (long long)tiles);
   a.roi_dev = roi_dev;
@@ -179,7 +204,10 @@ static cmp_status composite_depth_impl(const cmp_image* in, int32_t n, const int
     a.n = cnt;
     a.accumulate = base > 0;
     a.index_base = base;
-    hipLaunchKernelGGL(depth_kernel, dim3((unsigned)tiles), dim3(kThreads), 0, s, a);
+    if (small)
+      hipLaunchKernelGGL(depth_small_kernel, dim3((unsigned)tiles), dim3(kThreads), 0, s, a);
+    else
+      hipLaunchKernelGGL(depth_kernel, dim3((unsigned)tiles), dim3(kThreads), 0, s, a);
     CMP_CHECK_HIP(hipGetLastError());
     base += cnt;
   } while (base < n);

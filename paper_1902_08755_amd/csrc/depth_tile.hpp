@@ -32,7 +32,7 @@ struct DepthDesc {
 // viewport whose origin is (vx, vy) into out_color/out_depth. With
 // `accumulate`, the outputs already hold the result of earlier contributors
 // (a previous pass) and are combined under the same rule.
-constexpr int kDepthRows = 4;    // rows per lane per step
+constexpr int kDepthRows = 4;    // rows per lane per step, but for small views
 constexpr int kDepthBatch = 4;   // covering contributors whose loads are in flight together
 
 typedef const __attribute__((address_space(1))) uint32_t* GlobalU32;
@@ -93,27 +93,28 @@ __device__ __forceinline__ void stage_contributors(F desc, int n, const int32_t*
 // and scalar arithmetic for its row addresses (it replaces LDS reads made
 // uniform and tests of row and column per lane: 40 partial contributors over
 // 1920x1080 15.3 -> 14.7 us, 200 over 1281x719 68.7 -> 65.3).
-// kDepthBatch covering contributors x 4 rows are loaded at a time, so the
+// kDepthBatch covering contributors x kRows rows are loaded at a time, so the
 // depth loads of a typical step are one round trip; the winner's colour is
 // gathered at the end.
+template <int kRows>
 __device__ __forceinline__ void depth_tile(const DepthRec* rec, int n, int x0, int y0, int tw,
                                            int th, uint32_t* __restrict__ out_color,
                                            uint32_t* __restrict__ out_depth, int64_t out_pitch,
                                            int vx, int vy, bool accumulate) {
   typedef const __attribute__((address_space(1))) char* Bytes;
   const int lane = threadIdx.x % kWave, wave = uniform((int)(threadIdx.x / kWave));
-  constexpr int kStepRows = kDepthRows * (kThreads / kWave);
+  constexpr int kStepRows = kRows * (kThreads / kWave);
   for (int cx = 0; cx < tw; cx += kWave) {
     const int cx0 = x0 + cx, cols = min(kWave, tw - cx);   // the wave's columns
     const int X = cx0 + lane;
     const bool col_ok = lane < cols;
-    for (int r0 = wave * kDepthRows; r0 < th; r0 += kStepRows) {
-      const int Y0 = y0 + r0;                       // rows Y0 .. Y0 + 3 (uniform)
-      const int nrows = min(kDepthRows, th - r0);
-      uint32_t bd[kDepthRows], pc[kDepthRows];
-      int bi[kDepthRows];
+    for (int r0 = wave * kRows; r0 < th; r0 += kStepRows) {
+      const int Y0 = y0 + r0;                       // rows Y0 .. Y0 + kRows - 1 (uniform)
+      const int nrows = min(kRows, th - r0);
+      uint32_t bd[kRows], pc[kRows];
+      int bi[kRows];
 #pragma unroll
-      for (int k = 0; k < kDepthRows; ++k) {
+      for (int k = 0; k < kRows; ++k) {
         bd[k] = kClearDepth;
         pc[k] = 0;
         bi[k] = -1;
@@ -132,7 +133,7 @@ __device__ __forceinline__ void depth_tile(const DepthRec* rec, int n, int x0, i
         const int dx = __builtin_elementwise_sub_sat(R.x, cx0);
         const int dy = __builtin_elementwise_sub_sat(R.y, Y0);
         const int first = min(max(dx, 0), kWave), end = min(__builtin_elementwise_add_sat(dx, R.w), cols);
-        const int k0 = min(max(dy, 0), kDepthRows), k1 = min(__builtin_elementwise_add_sat(dy, R.h), nrows);
+        const int k0 = min(max(dy, 0), kRows), k1 = min(__builtin_elementwise_add_sat(dy, R.h), nrows);
         uint64_t cover = (uint64_t)__ballot(c0 + lane < n && first < end && k0 < k1);
         const uint64_t pb = (uint64_t)R.pitch * 4;
         // of row Y0 + k0, the first covered one
@@ -148,8 +149,8 @@ __device__ __forceinline__ void depth_tile(const DepthRec* rec, int n, int x0, i
           // one repeats the first and is ignored), then every load of the
           // batch, then the compares: no branch between the loads
           int ids[kDepthBatch];
-          uint32_t dv[kDepthBatch][kDepthRows];
-          bool ok[kDepthBatch][kDepthRows];
+          uint32_t dv[kDepthBatch][kRows];
+          bool ok[kDepthBatch][kRows];
           const int i0 = (int)__builtin_ctzll(cover);
 #pragma unroll
           for (int j = 0; j < kDepthBatch; ++j) {
@@ -167,7 +168,7 @@ __device__ __forceinline__ void depth_tile(const DepthRec* rec, int n, int x0, i
             const bool in_col = (uint32_t)lane - f < cnt;
             const uint32_t off = (in_col ? (uint32_t)lane : f) * 4u;
 #pragma unroll
-            for (int k = 0; k < kDepthRows; ++k) {
+            for (int k = 0; k < kRows; ++k) {
               dv[j][k] = *(GlobalU32)((Bytes)row + off);
               ok[j][k] = in_col && k >= a0 && k < a1;
               if (k >= a0 && k + 1 < a1) row += pitch;
@@ -177,7 +178,7 @@ __device__ __forceinline__ void depth_tile(const DepthRec* rec, int n, int x0, i
 #pragma unroll
           for (int j = 0; j < kDepthBatch; ++j) {
 #pragma unroll
-            for (int k = 0; k < kDepthRows; ++k) {
+            for (int k = 0; k < kRows; ++k) {
               if (ok[j][k] && dv[j][k] < bd[k]) {
                 bd[k] = dv[j][k];
                 bi[k] = ids[j];
@@ -190,9 +191,9 @@ __device__ __forceinline__ void depth_tile(const DepthRec* rec, int n, int x0, i
       // along the row across the wave; non-temporal stores, measured faster
       // here, while non-temporal loads were slower)
       if (col_ok) {
-        uint32_t cv[kDepthRows];
+        uint32_t cv[kRows];
 #pragma unroll
-        for (int k = 0; k < kDepthRows; ++k) {
+        for (int k = 0; k < kRows; ++k) {
           cv[k] = pc[k];
           if (k < nrows && bi[k] >= 0) {
             const DepthRec& R = rec[bi[k]];
@@ -200,7 +201,7 @@ __device__ __forceinline__ void depth_tile(const DepthRec* rec, int n, int x0, i
           }
         }
 #pragma unroll
-        for (int k = 0; k < kDepthRows; ++k) {
+        for (int k = 0; k < kRows; ++k) {
           if (k >= nrows) continue;
           const int64_t oo = (int64_t)(Y0 + k - vy) * out_pitch + (X - vx);
           __builtin_nontemporal_store(cv[k], &out_color[oo]);
