@@ -15,8 +15,8 @@
 // ballot lists the layers that reach the segment; each of them then costs
 // three lane reads, the cover test and one load (the loop it replaces read
 // every placement from LDS and made it uniform once per pixel row and layer,
-// about 19 vector instructions each: the 256 jobs of the batch took 2155 us
-// at 3.1 TB/s, now 1880 us at 3.6). Loads of up to over_batch layers are
+// about 19 vector instructions each: the 256 jobs of the batch took 2155 us,
+// and 1880 with this, before the batch's queues were divided). Loads of up to over_batch layers are
 // issued before the first of them is blended; the blend chain itself stays
 // strictly in order.
 #pragma once
@@ -212,7 +212,7 @@ __device__ __forceinline__ void over_tile_seq(const OverDesc* __restrict__ d, co
 // and a group is closed between two blends; a batch per group, which this
 // replaces, loaded and discarded most of its slots (40 partial FP16 layers in
 // 8 groups over 1921x1081: 203 us, bound by 2419 vector instructions per
-// wave; now 79 us).
+// wave; with full batches 79 us, 69 since XCDs take runs of tiles).
 template <int FMT>
 __device__ __forceinline__ void over_tile_tree(const OverDesc* __restrict__ d, int n, int groups,
                                                int x0, int y0, int tw, int th,

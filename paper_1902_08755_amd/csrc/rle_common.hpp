@@ -29,70 +29,6 @@ __host__ __device__ inline uint64_t rle_p0(uint64_t nb, int np) {
 }
 
 // ------------------------------------------------------------- helpers
-__device__ __forceinline__ uint64_t wave_incl_scan(uint64_t v) {
-  // DPP inside rows of 16 lanes (both halves of the word, then a 64-bit
-  // add), then the row totals of the lower rows read lane by lane
-#pragma unroll
-  for (int d = 1; d < 16; d <<= 1) {
-    uint32_t lo = 0, hi = 0;
-    switch (d) {
-      case 1: lo = __builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);
-              hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), 0x111, 0xF, 0xF, true); break;
-      case 2: lo = __builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
-              hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), 0x112, 0xF, 0xF, true); break;
-      case 4: lo = __builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
-              hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), 0x114, 0xF, 0xF, true); break;
-      default: lo = __builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
-               hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), 0x118, 0xF, 0xF, true); break;
-    }
-    v += ((uint64_t)hi << 32) | lo;
-  }
-  const uint32_t vlo = (uint32_t)v, vhi = (uint32_t)(v >> 32);
-  const uint64_t r0 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)vhi, 15) << 32) |
-                      (uint32_t)__builtin_amdgcn_readlane((int)vlo, 15);
-  const uint64_t r1 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)vhi, 31) << 32) |
-                      (uint32_t)__builtin_amdgcn_readlane((int)vlo, 31);
-  const uint64_t r2 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)vhi, 47) << 32) |
-                      (uint32_t)__builtin_amdgcn_readlane((int)vlo, 47);
-  const int row = (threadIdx.x % kWave) >> 4;
-  return v + (row >= 1 ? r0 : 0ull) + (row >= 2 ? r1 : 0ull) + (row >= 3 ? r2 : 0ull);
-}
-
-// Exclusive workgroup scan of two packed words (4 x 16-bit counters each);
-// also returns the workgroup totals. `sh` holds 8 words; ends with a barrier.
-__device__ __forceinline__ void block_scan2(uint64_t a, uint64_t b, uint64_t& ea, uint64_t& eb,
-                                            uint64_t& ta, uint64_t& tb, uint64_t* sh) {
-  const uint64_t ia = wave_incl_scan(a), ib = wave_incl_scan(b);
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  if (lane == kWave - 1) {
-    sh[wave] = ia;
-    sh[4 + wave] = ib;
-  }
-  __syncthreads();
-  uint64_t pa = 0, pb = 0;
-  ta = 0;
-  tb = 0;
-#pragma unroll
-  for (int w = 0; w < kThreads / kWave; ++w) {
-    if (w < wave) {
-      pa += sh[w];
-      pb += sh[4 + w];
-    }
-    ta += sh[w];
-    tb += sh[4 + w];
-  }
-  ea = pa + ia - a;
-  eb = pb + ib - b;
-  __syncthreads();
-}
-
-__device__ __forceinline__ uint32_t field16(uint64_t lo, uint64_t hi, int k) {
-  const uint64_t w = k < 4 ? lo : hi;
-  return (uint32_t)((w >> (16 * (k & 3))) & 0xFFFFu);
-}
-
-__device__ __forceinline__ uint32_t byte_of(uint32_t w, int k) { return (w >> (8 * (k & 3))) & 0xFFu; }
-
 // Bit swizzling (Section 5.5.1): bit 2j+b of component c moves to bit
 // 8j + 2c + b, i.e. the 4x4 matrix of 2-bit fields (component, significance
 // group) is transposed. Two delta swaps do the transpose: the off-diagonal
@@ -104,22 +40,6 @@ __device__ __forceinline__ uint32_t swizzle_bits(uint32_t x) {
   t = ((x >> 6) ^ x) & 0x00CC00CCu;
   x ^= t ^ (t << 6);
   return x;
-}
-
-// Clamp a device ROI to a W x H image.
-__device__ __forceinline__ void clamp_roi(const int32_t* roi_dev, int s, int W, int H, int& x,
-                                          int& y, int& w, int& h) {
-  if (!roi_dev) {
-    x = 0; y = 0; w = W; h = H;
-    return;
-  }
-  const int4 r = reinterpret_cast<const int4*>(roi_dev)[s];
-  x = min(max(r.x, 0), W);
-  y = min(max(r.y, 0), H);
-  w = min(max(r.z, 0), W - x);
-  h = min(max(r.w, 0), H - y);
-  if (w == 0 || h == 0) { x = 0; y = 0; w = 0; h = 0; }
-  x = uniform(x); y = uniform(y); w = uniform(w); h = uniform(h);
 }
 
 // ------------------------------------------------------------ compress
