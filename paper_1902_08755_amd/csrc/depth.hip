@@ -147,7 +147,10 @@ static cmp_status composite_depth_impl(const cmp_image* in, int32_t n, const int
               "out_depth is required when n > %d (it carries the result between passes)",
               kColorOnly);
   CMP_REQUIRE(((uintptr_t)roi_dev & 15) == 0, "roi_dev must be 16-byte aligned");
-  int tw = tile.w ? tile.w : 64, th = tile.h ? tile.h : 16;
+  const int64_t tiles16 = ((int64_t)viewport.w + 63) / 64 * (((int64_t)viewport.h + 15) / 16);
+  const bool small = tile.w == 0 && tile.h == 0 && tiles16 < kSmallTiles;
+  const int tw = tile.w ? tile.w : 64;
+  const int th = tile.h ? tile.h : small ? kSmallRows * (kThreads / kWave) : 16;
   CMP_REQUIRE(tw > 0 && th > 0 && (int64_t)tw * th <= 65536,
               "tile %dx%d: sizes must be positive, area <= 65536", tw, th);
 
@@ -155,13 +158,8 @@ static cmp_status composite_depth_impl(const cmp_image* in, int32_t n, const int
   memset(&a, 0, sizeof a);
   int64_t tiles = 0;
   Region reg[kMaxRegions];
-  int nreg = plan_regions(sched, viewport, tw, th, reg, &tiles);
+  const int nreg = plan_regions(sched, viewport, tw, th, reg, &tiles);
   if (nreg < 0) return nreg;
-  const bool small = tile.w == 0 && tile.h == 0 && tiles < kSmallTiles;
-  if (small) {
-    th = kSmallRows * (kThreads / kWave);
-    nreg = plan_regions(sched, viewport, tw, th, reg, &tiles);
-  }
   memcpy(a.words + kArgWords - nreg * kRegionWords, reg, nreg * sizeof(Region));
   CMP_REQUIRE(tiles < (1ll << 24), "too many tiles (%lld)", (long long)tiles);
   a.roi_dev = roi_dev;
