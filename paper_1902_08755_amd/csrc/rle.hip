@@ -124,9 +124,9 @@ __global__ __launch_bounds__(kThreads, 4) void rle_compress_kernel(const RleCArg
   // slot, whose workgroup writes the header-only stream). Wave 0 computes the
   // table (lane i: image i, n <= 64; one load) into LDS.
   __shared__ int4 t_roi[kRleMax];
-  __shared__ uint32_t t_slots[kRleMax], t_first[kRleMax + 1];
+  __shared__ uint32_t t_slots[kRleMax], t_first[kRleMax + 1], t_all;
   __shared__ int2 s_next;   // the slot drawn for the next iteration
-  slot_table(a, t_roi, t_slots, t_first);
+  slot_table(a, t_roi, t_slots, t_first, &t_all);
   const uint32_t ep = call_epoch(a);
   __syncthreads();
 
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kThreads, 4) void rle_compress_kernel(const RleCArg
       cur = s_next;
     }
   }
-  finish_call(a, ep);
+  finish_call(a, ep, t_all);
 }
 
 // ---------------------------------------------------------- decompress

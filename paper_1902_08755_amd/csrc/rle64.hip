@@ -59,9 +59,9 @@ __global__ __launch_bounds__(kThreads, 4) void rle64_compress_kernel(const RleCA
   __shared__ uint32_t s_excl;
   __shared__ int32_t s_poison;
   __shared__ int4 t_roi[kRleMax];
-  __shared__ uint32_t t_slots[kRleMax], t_first[kRleMax + 1];
+  __shared__ uint32_t t_slots[kRleMax], t_first[kRleMax + 1], t_all;
   __shared__ int2 s_next;   // the slot drawn for the next iteration
-  slot_table(a, t_roi, t_slots, t_first);
+  slot_table(a, t_roi, t_slots, t_first, &t_all);
   const uint32_t ep = call_epoch(a);
   __syncthreads();
   Drawer drawer = draw_start(t_first, a.n);
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(kThreads, 4) void rle64_compress_kernel(const RleCA
       cur = s_next;
     }
   }
-  finish_call(a, ep);
+  finish_call(a, ep, t_all);
 }
 
 // ---------------------------------------------------------- decompress

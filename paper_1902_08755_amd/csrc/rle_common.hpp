@@ -70,7 +70,7 @@ struct RleCArgs {
 static_assert(sizeof(RleCArgs) <= 4096, "kernel arguments must fit in 4 KiB");
 
 // Workspace: the ticket counters (one per image, each on its own 128-byte
-// line), control words (the call epoch on one line; the count of finished
+// line, beside a count of finished workgroups), control words (the call epoch on one line; the count of finished
 // workgroups and the most flags any call has used on another), then the
 // look-back flags. It is zero-filled once, before its first use; every call
 // leaves it ready for the next: the last workgroup to finish zeroes the
@@ -84,6 +84,8 @@ constexpr size_t kTicketBytes = (size_t)kRleMax * kTicketStride * 4;
 constexpr int kCtlDone = 32;   // word index of the finished-workgroup count
 constexpr int kCtlHwm = 33;    // word index of the most flags any call has used
 constexpr size_t kCtlBytes = 256;
+constexpr uint32_t kDoneGroups = 32;   // counts of finished workgroups at word 1 of ticket lines
+static_assert(kDoneGroups <= kRleMax, "one ticket line per group");
 constexpr uint32_t kEpochMask = (1u << 30) - 1;
 
 // look-back flag: epoch (30 bits) << 34 | status (2 bits) << 32 | value (32
@@ -110,7 +112,7 @@ __device__ __forceinline__ uint32_t call_epoch(const RleCArgs& a) {
 
 // Every workgroup ends here, after its last use of the tickets and flags:
 // the last one to arrive zeroes the tickets of this call's images and the
-// count, raises the flag high-water mark to this call's flags, and advances
+// counts, raises the flag high-water mark to this call's flags, and advances
 // the epoch, ready for the next call on the workspace; if the epoch wraps to
 // 0 it first zeroes the flags below the high-water mark.
 // Relaxed atomics suffice: every ticket access is a device-scope atomic, and
@@ -118,17 +120,38 @@ __device__ __forceinline__ uint32_t call_epoch(const RleCArgs& a) {
 // call reads the epoch after this kernel has ended. (An acquire-release
 // count, which writes back the L2 at each workgroup's exit, made a 16 x
 // 1920x1080 compression 40% slower.)
-__device__ __forceinline__ void finish_call(const RleCArgs& a, uint32_t ep) {
+// One counter takes 11 ns per workgroup, which is the end of the call where
+// the workgroups have at most two slots each (`slots`: of the call) and end
+// together: they are then counted in kDoneGroups groups, and each group's last
+// one counts for it (24 images of 1279x719, 944 slots for 1024 workgroups:
+// 23.1 -> 19.2 us, 6 of 1000x700: 21.0 -> 14.6, RL64 of 3 of 1268x997: 17.8 ->
+// 12.1, of 8 of 1920x1080, 1215 slots: 27.3 -> 24.8). With more slots, or few
+// workgroups, the second round trip costs more than the queue (RL64 of 16 of
+// 2100x1500: 56.0, 56.8 in groups; one image of 400x300: 12.1, 12.5).
+__device__ __forceinline__ void finish_call(const RleCArgs& a, uint32_t ep, uint32_t slots) {
   __shared__ int s_last;
   __syncthreads();
-  if (threadIdx.x == 0)
-    s_last = __hip_atomic_fetch_add(a.ctl + kCtlDone, 1u, __ATOMIC_RELAXED,
-                                    __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+  if (threadIdx.x == 0) {
+    auto arrive = [](uint32_t* c, uint32_t of) {
+      return __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == of - 1;
+    };
+    if (slots >= 2 * gridDim.x || gridDim.x <= 2 * kDoneGroups) {
+      s_last = arrive(a.ctl + kCtlDone, gridDim.x);
+    } else {
+      const uint32_t g = blockIdx.x % kDoneGroups;
+      s_last = arrive(a.tickets + g * kTicketStride + 1,
+                      (gridDim.x - g + kDoneGroups - 1) / kDoneGroups) &&
+               arrive(a.ctl + kCtlDone, kDoneGroups);
+    }
+  }
   __syncthreads();
   if (s_last) {
-    for (int i = threadIdx.x; i < a.n; i += kThreads)
+    for (int i = threadIdx.x; i < kRleMax; i += kThreads) {
       __hip_atomic_store(a.tickets + i * kTicketStride, 0u, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(a.tickets + i * kTicketStride + 1, 0u, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    }
     const uint32_t hwm =
         max(__hip_atomic_load(a.ctl + kCtlHwm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
             (uint32_t)a.nflags);
@@ -407,7 +430,7 @@ __device__ __forceinline__ uint32_t row_shr(uint32_t v) {
 // workgroup writes the header-only stream. t_first: see Drawer; workgroups
 // beyond the slots get none.
 __device__ __forceinline__ void slot_table(const RleCArgs& a, int4* t_roi, uint32_t* t_slots,
-                                           uint32_t* t_first) {
+                                           uint32_t* t_first, uint32_t* t_all) {
   const int tid = threadIdx.x, lane = tid % kWave;
   if (tid < kWave) {
     int lx = 0, ly = 0, lw = 0, lh = 0;
@@ -439,7 +462,10 @@ __device__ __forceinline__ void slot_table(const RleCArgs& a, int4* t_roi, uint3
                                ? incl - min(incl, (uint32_t)lane + 1u)
                                : (uint32_t)((float)incl * ((float)rest / (float)all));
     t_first[lane + 1] = lane >= a.n - 1 ? rest : min(share, rest);
-    if (lane == 0) t_first[0] = 0;
+    if (lane == 0) {
+      t_first[0] = 0;
+      *t_all = all;
+    }
   }
 }
 
