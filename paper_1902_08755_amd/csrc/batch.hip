@@ -20,9 +20,15 @@
 // Items of 64 KB, 60 jobs: 109 us; 256 jobs of 64 to 2048 pixels a side, one
 // set of buffers: 1600 us (a single queue with items of 512 KB: 1841, of 128
 // KB: 1698; queues and items of 32 KB: 1638, of 128 KB: 1707; runs of 1, 16,
-// 64 items instead of 4: 1662, 1610, 1649). A completion counter lets the last
+// 64 items instead of 4: 1662, 1610, 1649). Completion counters let the last
 // workgroup reset the queues, so a captured graph can replay the launch
 // without any reset node.
+//
+// The end of a batch is kept short as well: the first workgroup that finds all
+// queues empty marks their counters, so that the others see it in their own
+// draws; finished workgroups are counted per queue first; and a batch of no
+// more items than workgroups draws and counts nothing (8 jobs of up to
+// 512x512: 26.6 -> 12.1 us; 100 of up to 256x256: 55.7 -> 51.2).
 //
 // Each item runs the same tile body as the plain launch, so a job's pixels
 // are bit-identical to cmp_composite_depth / cmp_composite_over (SEQ).
@@ -64,8 +70,8 @@ struct Item {
 };
 
 struct BatchArgs {
-  uint32_t* ctl;            // kQueues draw counters, then the finished workgroups,
-                            // one every kCtlWords
+  uint32_t* ctl;            // kQueues draw counters, kQueues counts of finished
+                            // workgroups and one of queues, one every kCtlWords
   const JobRec* jobs;
   const DepthDesc* ddesc;
   const OverDesc* odesc;
@@ -86,25 +92,41 @@ __device__ __forceinline__ int item_of(int q, int k) {
 __device__ __forceinline__ int first_items(int q) {
   return ((int)gridDim.x - q + kQueues - 1) / kQueues;
 }
-__device__ __forceinline__ int draw(uint32_t* c) {
-  return (int)__hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ uint32_t draw(uint32_t* c) {
+  return __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t drawn_so_far(uint32_t* c) {
+  return __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Item of a draw of queue q; at least nitems if that queue is empty. A draw of
+// kAllEmpty or more says that every queue is: without that mark each of the
+// workgroups looked through all the counters at the end.
+constexpr uint32_t kAllEmpty = 1u << 30;
+__device__ __forceinline__ int item_drawn(int q, uint32_t d, int nitems) {
+  return d < kAllEmpty ? item_of(q, first_items(q) + (int)d) : nitems;
 }
 
 // An item of any queue, nitems if all are empty (item_of grows with k, so an
 // empty queue stays empty, and a failed draw means that another one emptied).
 // The queues after q come first, so that the workgroups of one XCD spread.
 __device__ __forceinline__ int steal(uint32_t* ctl, int nitems, int q) {
+  if (drawn_so_far(ctl + q * kCtlWords) >= kAllEmpty) return nitems;
   while (true) {
-    int c[kQueues], from = -1;
+    uint32_t c[kQueues];
+    int from = -1;
+#pragma unroll
+    for (int k = 0; k < kQueues; ++k) c[k] = drawn_so_far(ctl + k * kCtlWords);
 #pragma unroll
     for (int k = 0; k < kQueues; ++k)
-      c[k] = (int)__hip_atomic_load(ctl + k * kCtlWords, __ATOMIC_RELAXED,
-                                    __HIP_MEMORY_SCOPE_AGENT);
+      if (item_drawn(k, c[k], nitems) < nitems && (from < 0 || (k > q && from < q))) from = k;
+    if (from < 0) {
 #pragma unroll
-    for (int k = 0; k < kQueues; ++k)
-      if (item_of(k, first_items(k) + c[k]) < nitems && (from < 0 || (k > q && from < q))) from = k;
-    if (from < 0) return nitems;
-    const int it = item_of(from, first_items(from) + draw(ctl + from * kCtlWords));
+      for (int k = 0; k < kQueues; ++k)
+        __hip_atomic_fetch_or(ctl + k * kCtlWords, kAllEmpty, __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_AGENT);
+      return nitems;
+    }
+    const int it = item_drawn(from, draw(ctl + from * kCtlWords), nitems);
     if (it < nitems) return it;
   }
 }
@@ -119,9 +141,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))
   const int tid = threadIdx.x;
   const int q = (int)blockIdx.x % kQueues;
   int it = item_of(q, (int)blockIdx.x / kQueues);
+  // all items are first items of some workgroup: no draws, nothing to reset.
+  // (The first items of whole groups of kQueues * kRun workgroups are exactly
+  // the items up to their number; those of an incomplete group are not.)
+  const bool once = a.nitems <= (int)gridDim.x / (kQueues * kRun) * (kQueues * kRun);
   while (it < a.nitems) {   // uniform
-    int drawn = 0;
-    if (tid == 0) drawn = draw(a.ctl + q * kCtlWords);
+    uint32_t drawn = 0;
+    if (tid == 0 && !once) drawn = draw(a.ctl + q * kCtlWords);
     const Item I = a.items[it];
     const JobRec& J = a.jobs[uniform(I.job)];
     const int t1 = min(uniform(I.tile0) + uniform(J.per_item), uniform(J.ntiles));
@@ -160,18 +186,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))
         }
       }
     }
+    if (once) return;   // uniform
     if (tid == 0) {
-      const int next = item_of(q, first_items(q) + drawn);
-      s_item = next < a.nitems ? next : steal(a.ctl, a.nitems, q);
+      const int next = item_drawn(q, drawn, a.nitems);
+      s_item = next < a.nitems || drawn >= kAllEmpty ? next : steal(a.ctl, a.nitems, q);
     }
     __syncthreads();   // also: a depth job's records are no longer read
     it = uniform(s_item);
     __syncthreads();
   }
-  if (tid == 0) {
-    // no fence: nothing but the counters is shared with the last workgroup
-    if (draw(a.ctl + kQueues * kCtlWords) == (int)gridDim.x - 1) {
-      for (int k = 0; k <= kQueues; ++k)
+  if (tid == 0 && !once) {
+    // no fence: nothing but the counters is shared with the last workgroup.
+    // Counted by queue first: 1536 workgroups that end together would queue 17
+    // us at one counter.
+    uint32_t* done = a.ctl + kQueues * kCtlWords;
+    if (draw(done + q * kCtlWords) == (uint32_t)first_items(q) - 1 &&
+        draw(done + kQueues * kCtlWords) == min(gridDim.x, (unsigned)kQueues) - 1) {
+      for (int k = 0; k <= 2 * kQueues; ++k)
         __hip_atomic_store(&a.ctl[k * kCtlWords], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
@@ -402,7 +433,7 @@ extern "C" cmp_status cmp_batch_plan_create(const cmp_job* jobs, int32_t njobs,
                    [](const Items& x, const Items& y) { return x.cost > y.cost; });
   P->nitems = (int32_t)nitems;
   // device table layout
-  P->off_jobs = (kQueues + 1) * kCtlWords * sizeof(uint32_t);
+  P->off_jobs = (2 * kQueues + 1) * kCtlWords * sizeof(uint32_t);
   P->off_ddesc = align_up(P->off_jobs + recs.size() * sizeof(JobRec), 64);
   P->off_odesc = align_up(P->off_ddesc + dd.size() * sizeof(DepthDesc), 64);
   P->off_items = align_up(P->off_odesc + od.size() * sizeof(OverDesc), 64);
