@@ -17,6 +17,8 @@
 // The loads of four contributors x four rows are issued before any compare.
 #pragma once
 
+#include <type_traits>
+
 #include "cmp_internal.hpp"
 
 namespace cmp {
@@ -144,16 +146,17 @@ __device__ __forceinline__ void depth_tile(const DepthRec* rec, int n, int x0, i
         auto of_lane = [](uint32_t v, int i) {
           return (uint32_t)__builtin_amdgcn_readlane((int)v, i);
         };
-        while (cover) {   // uniform
-          // the next kDepthBatch covering contributors (a slot past the last
-          // one repeats the first and is ignored), then every load of the
-          // batch, then the compares: no branch between the loads
-          int ids[kDepthBatch];
-          uint32_t dv[kDepthBatch][kRows];
-          bool ok[kDepthBatch][kRows];
+        // the next N covering contributors (a slot past the last one repeats
+        // the first and is ignored), then every load of the batch, then the
+        // compares: no branch between the loads
+        auto batch = [&](auto size) {
+          constexpr int N = decltype(size)::value;
+          int ids[N];
+          uint32_t dv[N][kRows];
+          bool ok[N][kRows];
           const int i0 = (int)__builtin_ctzll(cover);
 #pragma unroll
-          for (int j = 0; j < kDepthBatch; ++j) {
+          for (int j = 0; j < N; ++j) {
             const bool has = cover != 0;
             const int i = has ? (int)__builtin_ctzll(cover) : i0;
             cover &= cover - 1;
@@ -176,7 +179,7 @@ __device__ __forceinline__ void depth_tile(const DepthRec* rec, int n, int x0, i
           }
           // ascending indices and a strict "<": ties keep the lower index
 #pragma unroll
-          for (int j = 0; j < kDepthBatch; ++j) {
+          for (int j = 0; j < N; ++j) {
 #pragma unroll
             for (int k = 0; k < kRows; ++k) {
               if (ok[j][k] && dv[j][k] < bd[k]) {
@@ -185,7 +188,12 @@ __device__ __forceinline__ void depth_tile(const DepthRec* rec, int n, int x0, i
               }
             }
           }
-        }
+        };
+        // (the last two or one in a smaller batch: 40 partial contributors over
+        // 1920x1080 13.2 -> 12.6 us, 100 30.6 -> 30.2)
+        int left = (int)__builtin_popcountll(cover);   // uniform
+        for (; left > 2; left -= kDepthBatch) batch(std::integral_constant<int, kDepthBatch>());
+        if (left > 0) batch(std::integral_constant<int, 2>());
       }
       // gather the winners' colours and store (4-byte accesses, coalesced
       // along the row across the wave; non-temporal stores, measured faster
