@@ -124,6 +124,9 @@ __device__ __forceinline__ int steal(uint32_t* ctl, int nitems, int q) {
       for (int k = 0; k < kQueues; ++k)
         __hip_atomic_fetch_or(ctl + k * kCtlWords, kAllEmpty, __ATOMIC_RELAXED,
                               __HIP_MEMORY_SCOPE_AGENT);
+      // every mark is made before this workgroup counts as finished: one that
+      // arrived after the last workgroup's reset would empty the next launch
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       return nitems;
     }
     const int it = item_drawn(from, draw(ctl + from * kCtlWords), nitems);
