@@ -151,14 +151,26 @@ __global__ __launch_bounds__(kThreads) void roi_kernel(const RoiArgs a) {
 #pragma unroll
     for (int k = 0; k < kRoiBatch; ++k) examine(k);
   } else {
-    // an image narrower than a unit: pixel by pixel
-    for (int t = threadIdx.x; t < I.w * nrows; t += kThreads) {
-      const int r = t / I.w, x = t - r * I.w;
-      if (px_mask<MODE>(base + (int64_t)(y0 + r) * row_bytes, x)) {
-        minx = min(minx, x);
-        maxx = max(maxx, x);
-        miny = min(miny, y0 + r);
-        maxy = max(maxy, y0 + r);
+    // an image narrower than a unit: column by column, a row per lane, and
+    // kRoiBatch rows in flight (a row past the band's end repeats the last one;
+    // a box does not mind). One load at a time per lane was bound by its
+    // latency where a band has many rows (3 x 4000000: 52.8 us, now 17.9).
+    for (int r0 = threadIdx.x; r0 < nrows; r0 += kThreads * kRoiBatch) {
+      for (int x = 0; x < I.w; ++x) {   // uniform
+        uint32_t m[kRoiBatch];
+#pragma unroll
+        for (int k = 0; k < kRoiBatch; ++k)
+          m[k] = px_mask<MODE>(base + (int64_t)(y0 + min(r0 + k * kThreads, nrows - 1)) * row_bytes, x);
+#pragma unroll
+        for (int k = 0; k < kRoiBatch; ++k) {
+          if (m[k]) {
+            const int y = y0 + min(r0 + k * kThreads, nrows - 1);
+            minx = min(minx, x);
+            maxx = max(maxx, x);
+            miny = min(miny, y);
+            maxy = max(maxy, y);
+          }
+        }
       }
     }
   }
