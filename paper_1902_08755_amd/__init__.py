@@ -228,7 +228,7 @@ def _c_images(colors: Sequence, depths: Optional[Sequence], rois: Sequence, rgba
         if not exact:
             raise struct.error
         struct.pack_into("<" + "QQqiiii" * n, arr, 0, *flat)
-    except struct.error:   # rectangles of other numbers than 32-bit integers
+    except (struct.error, TypeError):   # rectangles of other numbers than 32-bit integers
         at = 0
         for i, roi in enumerate(rois):
             arr[i] = CImage(flat[at] or None, flat[at + 1] or None, flat[at + 2], _rect(roi))
