@@ -314,16 +314,18 @@ def _over(rgba: Sequence, rois: Sequence, order, viewport, out, schedule, tile, 
 
 def composite_over_backward(layers: Sequence, order, viewport, grad_out, grads=None, stream=None):
     """Adjoint of composite_over: d loss / d layer for every layer, in FP32, or
-    in FP16 where all of ``grads`` are float16 tensors."""
+    in FP16 where all of ``grads`` are float16 tensors (no other types, no mix)."""
     rgba, rois = [_color_of(l) for l in layers], [l.roi for l in layers]
     if grads is None:
         grads = [torch.empty((int(o[3]), int(o[2]), 4), dtype=torch.float32, device=r.device)
                  for o, r in zip(rois, rgba)]
-    half = sum(g.dtype == torch.float16 for g in grads)
-    if half not in (0, len(grads)):
-        raise ValueError("grads mix float16 with other types")
+    # the kernel stores pixels of one of the two formats through every pointer
+    dtype = grads[0].dtype if grads else torch.float32
+    if dtype not in (torch.float32, torch.float16) or any(g.dtype != dtype for g in grads):
+        raise ValueError("grads must be all float32 or all float16")
     return _over_backward(rgba, rois, order, viewport, grad_out, grads,
-                          RGBA16F if half else RGBA32F, [_rgba_pitch(g) for g in grads], stream)
+                          RGBA16F if dtype == torch.float16 else RGBA32F,
+                          [_rgba_pitch(g) for g in grads], stream)
 
 
 def _over_backward(rgba: Sequence, rois: Sequence, order, viewport, grad_out, grads,

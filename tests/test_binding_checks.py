@@ -22,3 +22,15 @@ def test_rectangles_of_other_numbers(roi):
     want = [(9, 8, 7, 0), tuple(int(v) for v in roi)]
     assert [(a.roi.x, a.roi.y, a.roi.w, a.roi.h) for a in arr] == want
     assert [a.pitch for a in arr] == [7, 5]
+
+
+@pytest.mark.parametrize("types", [[torch.bfloat16], [torch.float64], [torch.bfloat16] * 3,
+                                   [torch.float32, torch.float16], [torch.float16, torch.float32],
+                                   [torch.float32, torch.float64], [torch.int32]])
+def test_gradient_types(types):
+    """Gradients that the kernel would write past the end of, or as other numbers."""
+    layers = [cmp.Image(_empty(), None, (0, 0, 7, 0)) for _ in types]
+    grads = [torch.zeros((2, 7, 4), dtype=t) for t in types]
+    with pytest.raises(ValueError, match="all float32 or all float16"):
+        cmp.composite_over_backward(layers, list(range(len(types))), (0, 0, 7, 2),
+                                    torch.zeros((2, 7, 4)), grads=grads)
