@@ -186,10 +186,12 @@ class Image:
     roi: tuple
 
 
-def _c_images(colors: Sequence, depths: Optional[Sequence], rois: Sequence, rgba: bool):
+def _c_images(colors: Sequence, depths: Optional[Sequence], rois: Sequence, rgba: bool,
+              dtype: Optional[torch.dtype] = None):
     """The CImage array of n contributors, written by one struct.pack_into from
     a flat list: 53 us for 80 layers, where a ctypes object per image and
-    rectangle took 134."""
+    rectangle took 134. With `dtype`, which the call's pixel format stands for,
+    pixels of another type are refused: they would be read out of range."""
     n = len(colors)
     arr = (CImage * max(1, n))()
     flat, exact = [], True
@@ -203,6 +205,9 @@ def _c_images(colors: Sequence, depths: Optional[Sequence], rois: Sequence, rgba
             if rgba:
                 if len(shape) != 3 or shape[2] != 4 or strides[1:] != (4, 1) or strides[0] % 4:
                     raise ValueError("expected a (h, pitch, 4) RGBA tensor")
+                if (dtype is not None and color.dtype != dtype
+                        and int(roi[2]) > 0 and int(roi[3]) > 0):
+                    raise ValueError(f"image {i}: expected {dtype} pixels, got {color.dtype}")
                 pitch = strides[0] // 4
             else:
                 if len(shape) != 2 or strides[1] != 1 or color.element_size() != 4:
@@ -302,12 +307,13 @@ def _over(rgba: Sequence, rois: Sequence, order, viewport, out, schedule, tile, 
     x, y, w, h = viewport
     n = len(rgba)
     fmt = _fmt_of(rgba[0]) if n else RGBA32F
+    arr = _c_images(rgba, None, rois, True, rgba[0].dtype if n else None)
     if out is None:
         out = torch.empty((h, w, 4), dtype=torch.float32, device=_dev())
     order_arr = _order(order, n)
-    st = lib().cmp_composite_over(_c_images(rgba, None, rois, True), n, fmt, order_arr,
-                                  _rect(viewport), out.data_ptr(), _rgba_pitch(out),
-                                  _schedule(schedule), Tile(*tile), _stream(stream))
+    st = lib().cmp_composite_over(arr, n, fmt, order_arr, _rect(viewport), out.data_ptr(),
+                                  _rgba_pitch(out), _schedule(schedule), Tile(*tile),
+                                  _stream(stream))
     _check(st, "cmp_composite_over")
     return out
 
@@ -332,15 +338,15 @@ def _over_backward(rgba: Sequence, rois: Sequence, order, viewport, grad_out, gr
                    grad_fmt: int, pitches: Sequence, stream):
     n = len(rgba)
     fmt = _fmt_of(rgba[0]) if n else RGBA32F
+    arr = _c_images(rgba, None, rois, True, rgba[0].dtype if n else None)
     ptrs = (ctypes.c_void_p * max(1, n))(*[g.data_ptr() for g in grads])
     pitches = (ctypes.c_int64 * max(1, n))(*pitches)
     order_arr = _order(order, n)
     grad_out = grad_out.contiguous()
     need = lib().cmp_over_backward_workspace_size(n)
     ws = workspace("over_backward", need) if need else None
-    st = lib().cmp_composite_over_backward_as(_c_images(rgba, None, rois, True), n, fmt, order_arr,
-                                              _rect(viewport), grad_out.data_ptr(),
-                                              _rgba_pitch(grad_out), ptrs,
+    st = lib().cmp_composite_over_backward_as(arr, n, fmt, order_arr, _rect(viewport),
+                                              grad_out.data_ptr(), _rgba_pitch(grad_out), ptrs,
                                               grad_fmt, pitches,
                                               ws.data_ptr() if ws is not None else None,
                                               ws.numel() if ws is not None else 0,

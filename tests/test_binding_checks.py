@@ -34,3 +34,24 @@ def test_gradient_types(types):
     with pytest.raises(ValueError, match="all float32 or all float16"):
         cmp.composite_over_backward(layers, list(range(len(types))), (0, 0, 7, 2),
                                     torch.zeros((2, 7, 4)), grads=grads)
+
+
+@pytest.mark.parametrize("first,other", [(torch.float32, torch.float16),
+                                         (torch.float16, torch.float32),
+                                         (torch.float16, torch.bfloat16)])
+def test_layers_of_several_types(first, other):
+    """One pixel format per call: a layer of another type would be read as the
+    first one's, out of range where its pixels are smaller."""
+    rois, order, vp = [(0, 0, 7, 0), (0, 0, 7, 2)], [1, 0], (0, 0, 7, 2)
+    pixels = [_empty(first), torch.zeros((2, 7, 4), dtype=other)]
+    layers = [cmp.Image(t, None, r) for t, r in zip(pixels, rois)]
+    out, match = torch.zeros((2, 7, 4)), f"expected {first} pixels, got {other}"
+    with pytest.raises(ValueError, match=match):
+        cmp.composite_over(layers, order, vp, out=out)
+    with pytest.raises(ValueError, match=match):
+        cmp.composite_over_backward(layers, order, vp, out)
+    with pytest.raises(ValueError, match=match):
+        cmp.OverComposite.apply(order, vp, rois, *pixels)
+    # a layer that covers nothing is not read: refused for its device only
+    with pytest.raises(ValueError, match="device tensor"):
+        cmp.composite_over([layers[0], cmp.Image(pixels[1], None, (0, 0, 0, 0))], order, vp, out=out)
