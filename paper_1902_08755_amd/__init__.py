@@ -250,6 +250,18 @@ def _images(imgs: Sequence, kind: str):
     return _c_images(colors, depths, rois, kind == "rgba")
 
 
+def _images_of(imgs: Sequence, fmt: int):
+    """The CImage array of images in pixel format `fmt`."""
+    if fmt == RGBA8:
+        return _images(imgs, "u32")
+    size = 16 if fmt == RGBA32F else 8
+    for i, im in enumerate(imgs):
+        color = _color_of(im)
+        if 0 not in color.shape and 4 * color.element_size() != size:
+            raise ValueError(f"image {i}: expected pixels of {size} bytes, got {color.dtype}")
+    return _images(imgs, "rgba")
+
+
 def _color_of(im) -> torch.Tensor:
     return im.color if hasattr(im, "color") else im.rgba
 
@@ -455,7 +467,7 @@ def roi_detect(images: Sequence, fmt: int = RGBA8, roi_out=None, ws=None, stream
     Without `ws` the call uses a workspace shared by all calls on the device:
     calls that may overlap (on other streams) must each pass their own."""
     n = len(images)
-    arr = _images(images, "rgba" if fmt != RGBA8 else "u32")
+    arr = _images_of(images, fmt)
     if roi_out is None:
         roi_out = torch.empty((n, 4), dtype=torch.int32,
                               device=_dev())
@@ -474,10 +486,10 @@ def roi_grid(images: Sequence, cell, fmt: int = RGBA8, stream=None):
     cw, ch = cell
     dims = [((int(im.roi[3]) + ch - 1) // ch, (int(im.roi[2]) + cw - 1) // cw) for im in images]
     total = sum(a * b for a, b in dims)
+    arr = _images_of(images, fmt)
     buf = torch.zeros(max(1, total), dtype=torch.uint8,
                       device=_dev())
-    st = lib().cmp_roi_grid(_images(images, "rgba" if fmt != RGBA8 else "u32"), len(images), fmt,
-                            cw, ch, buf.data_ptr(), _stream(stream))
+    st = lib().cmp_roi_grid(arr, len(images), fmt, cw, ch, buf.data_ptr(), _stream(stream))
     _check(st, "cmp_roi_grid")
     out, o = [], 0
     for gh, gw in dims:

@@ -55,3 +55,15 @@ def test_layers_of_several_types(first, other):
     # a layer that covers nothing is not read: refused for its device only
     with pytest.raises(ValueError, match="device tensor"):
         cmp.composite_over([layers[0], cmp.Image(pixels[1], None, (0, 0, 0, 0))], order, vp, out=out)
+
+
+@pytest.mark.parametrize("fmt,dtype", [(cmp.RGBA32F, torch.float16), (cmp.RGBA32F, torch.int16),
+                                       (cmp.RGBA16F, torch.float32), (cmp.RGBA16F, torch.uint8)])
+def test_roi_pixels_of_the_format(fmt, dtype):
+    """Float images whose pixels are not the size of the format's."""
+    imgs = [cmp.Image(_empty(), None, (0, 0, 7, 0)),
+            cmp.Image(torch.zeros((2, 7, 4), dtype=dtype), None, (0, 0, 7, 2))]
+    with pytest.raises(ValueError, match="expected pixels of"):
+        cmp.roi_detect(imgs, fmt=fmt)
+    with pytest.raises(ValueError, match="expected pixels of"):
+        cmp.roi_grid(imgs, (4, 4), fmt=fmt)
