@@ -166,6 +166,13 @@ def _rgba_pitch(t: torch.Tensor) -> int:
     return t.stride(0) // 4
 
 
+def _rgba32_pitch(t: torch.Tensor, what: str) -> int:
+    """The pitch of FP32 pixels: smaller ones would be passed over the end of."""
+    if t.element_size() != 4:
+        raise ValueError(f"{what} must hold float32 pixels, got {t.dtype}")
+    return _rgba_pitch(t)
+
+
 def _cuda(t: Optional[torch.Tensor], what: str):
     if t is None:
         return None
@@ -322,10 +329,10 @@ def _over(rgba: Sequence, rois: Sequence, order, viewport, out, schedule, tile, 
     arr = _c_images(rgba, None, rois, True, rgba[0].dtype if n else None)
     if out is None:
         out = torch.empty((h, w, 4), dtype=torch.float32, device=_dev())
+    pitch = _rgba32_pitch(out, "out")
     order_arr = _order(order, n)
-    st = lib().cmp_composite_over(arr, n, fmt, order_arr, _rect(viewport), out.data_ptr(),
-                                  _rgba_pitch(out), _schedule(schedule), Tile(*tile),
-                                  _stream(stream))
+    st = lib().cmp_composite_over(arr, n, fmt, order_arr, _rect(viewport), out.data_ptr(), pitch,
+                                  _schedule(schedule), Tile(*tile), _stream(stream))
     _check(st, "cmp_composite_over")
     return out
 
@@ -355,11 +362,11 @@ def _over_backward(rgba: Sequence, rois: Sequence, order, viewport, grad_out, gr
     pitches = (ctypes.c_int64 * max(1, n))(*pitches)
     order_arr = _order(order, n)
     grad_out = grad_out.contiguous()
+    grad_pitch = _rgba32_pitch(grad_out, "grad_out")
     need = lib().cmp_over_backward_workspace_size(n)
     ws = workspace("over_backward", need) if need else None
     st = lib().cmp_composite_over_backward_as(arr, n, fmt, order_arr, _rect(viewport),
-                                              grad_out.data_ptr(), _rgba_pitch(grad_out), ptrs,
-                                              grad_fmt, pitches,
+                                              grad_out.data_ptr(), grad_pitch, ptrs, grad_fmt, pitches,
                                               ws.data_ptr() if ws is not None else None,
                                               ws.numel() if ws is not None else 0,
                                               _stream(stream))

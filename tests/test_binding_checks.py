@@ -67,3 +67,14 @@ def test_roi_pixels_of_the_format(fmt, dtype):
         cmp.roi_detect(imgs, fmt=fmt)
     with pytest.raises(ValueError, match="expected pixels of"):
         cmp.roi_grid(imgs, (4, 4), fmt=fmt)
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float64])
+def test_composite_and_its_gradient_are_float32(dtype):
+    """The composite is written, and its gradient read, at 16 bytes per pixel."""
+    layers, vp = [cmp.Image(_empty(), None, (0, 0, 7, 0))], (0, 0, 7, 2)
+    other = torch.zeros((2, 7, 4), dtype=dtype)
+    with pytest.raises(ValueError, match="out must hold float32"):
+        cmp.composite_over(layers, [0], vp, out=other)
+    with pytest.raises(ValueError, match="grad_out must hold float32"):
+        cmp.composite_over_backward(layers, [0], vp, other)
