@@ -14,10 +14,13 @@ Image conventions (matching cmp.h):
 """
 from __future__ import annotations
 
+import collections
+import contextlib
 import ctypes
 import functools
 import os
 import struct
+import threading
 from dataclasses import dataclass
 from typing import Optional, Sequence
 
@@ -167,7 +170,7 @@ def _rgba_pitch(t: torch.Tensor) -> int:
 
 
 def _rgba32_pitch(t: torch.Tensor, what: str) -> int:
-    """The pitch of FP32 pixels: smaller ones would be passed over the end of."""
+    """The pitch of FP32 pixels (a buffer of smaller ones would be overrun)."""
     if t.element_size() != 4:
         raise ValueError(f"{what} must hold float32 pixels, got {t.dtype}")
     return _rgba_pitch(t)
@@ -363,10 +366,16 @@ def _over_backward(rgba: Sequence, rois: Sequence, order, viewport, grad_out, gr
     order_arr = _order(order, n)
     grad_out = grad_out.contiguous()
     grad_pitch = _rgba32_pitch(grad_out, "grad_out")
+    # the layer descriptors of a pass with more than 64 layers: of this call
+    # alone (copied there by launches of their own), in its stream's order
     need = lib().cmp_over_backward_workspace_size(n)
-    ws = workspace("over_backward", need) if need else None
+    ws = None
+    if need:
+        with _on(stream):
+            ws = torch.empty(need, dtype=torch.uint8, device=_dev())
     st = lib().cmp_composite_over_backward_as(arr, n, fmt, order_arr, _rect(viewport),
-                                              grad_out.data_ptr(), grad_pitch, ptrs, grad_fmt, pitches,
+                                              grad_out.data_ptr(), grad_pitch, ptrs, grad_fmt,
+                                              pitches,
                                               ws.data_ptr() if ws is not None else None,
                                               ws.numel() if ws is not None else 0,
                                               _stream(stream))
@@ -454,25 +463,47 @@ def assemble_pixels(images: Sequence, offsets, kernel, viewport, out=None, strea
 
 
 # -------------------------------------------------------------------- ROI
-_workspaces = {}
+_workspaces = collections.OrderedDict()   # (tag, device, stream) -> workspace, last used last
+_workspaces_lock = threading.Lock()
+_WORKSPACES_KEPT = 64
 
 
-def workspace(tag: str, nbytes: int, device=None) -> torch.Tensor:
-    """A zero-filled device workspace cached per (tag, device); grown on demand.
-    The library leaves every workspace ready for its next call."""
-    dev = _dev() if device is None else device
-    key = (tag, str(dev))
-    ws = _workspaces.get(key)
-    if ws is None or ws.numel() < nbytes:
-        ws = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=dev)
-        _workspaces[key] = ws
-    return ws
+def _on(stream):
+    """Where torch allocates and fills in the order of `stream` (None: the current one)."""
+    return contextlib.nullcontext() if stream is None else torch.cuda.stream(stream)
+
+
+def workspace(tag: str, nbytes: int, device=None, stream=None) -> torch.Tensor:
+    """A zero-filled device workspace for a call that is one launch on `stream`
+    (None: the current one), cached per (tag, device, stream) and grown on
+    demand; the least recently used of more than 64 are given back. The library
+    leaves every workspace ready for its next call, and calls on one stream
+    follow one another, from whichever threads; calls on several may overlap, so
+    each stream has its own, allocated and filled in its order. A call that is
+    captured gets one of its own, which the graph fills and keeps: the graph may
+    run on any stream, beside other calls, after a cached one has been grown."""
+    with _on(stream):
+        dev = _dev() if device is None else torch.device(device)
+        handle = None
+        if dev.type == "cuda":
+            index = torch.cuda.current_device() if dev.index is None else dev.index
+            handle = torch._C._cuda_getCurrentRawStream(index)
+            if torch.cuda.is_current_stream_capturing():
+                return torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=dev)
+        key = (tag, dev, handle)
+        with _workspaces_lock:
+            ws = _workspaces.pop(key, None)
+            if ws is None or ws.numel() < nbytes:
+                ws = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=dev)
+            _workspaces[key] = ws
+            if len(_workspaces) > _WORKSPACES_KEPT:
+                _workspaces.popitem(last=False)
+        return ws
 
 
 def roi_detect(images: Sequence, fmt: int = RGBA8, roi_out=None, ws=None, stream=None):
     """Automatic ROI detection (cmp_roi_detect); returns an int32 (n, 4) tensor.
-    Without `ws` the call uses a workspace shared by all calls on the device:
-    calls that may overlap (on other streams) must each pass their own."""
+    Without `ws` the call uses its stream's (see :func:`workspace`)."""
     n = len(images)
     arr = _images_of(images, fmt)
     if roi_out is None:
@@ -480,7 +511,7 @@ def roi_detect(images: Sequence, fmt: int = RGBA8, roi_out=None, ws=None, stream
                               device=_dev())
     need = lib().cmp_roi_workspace_size(arr, n)
     if ws is None:
-        ws = workspace("roi", need)
+        ws = workspace("roi", need, stream=stream)
     st = lib().cmp_roi_detect(arr, n, fmt, roi_out.data_ptr(), ws.data_ptr(), ws.numel(),
                               _stream(stream))
     _check(st, "cmp_roi_detect")
@@ -631,7 +662,7 @@ def rle64_compress(images: Sequence, roi_dev=None, stream=None):
     cap_arr = (ctypes.c_uint64 * max(1, n))(*caps)
     sizes = torch.zeros(n, dtype=torch.int64, device=dev)
     status = torch.zeros(n, dtype=torch.int32, device=dev)
-    ws = workspace("rle64", int(L.cmp_rle_workspace_size(arr, n)))
+    ws = workspace("rle64", int(L.cmp_rle_workspace_size(arr, n)), stream=stream)
     st = L.cmp_rle64_compress(arr, n, RGBA8, _cuda(roi_dev, "roi_dev"), out_ptrs, cap_arr,
                               sizes.data_ptr(), status.data_ptr(), ws.data_ptr(), ws.numel(),
                               _stream(stream))

@@ -78,3 +78,16 @@ def test_composite_and_its_gradient_are_float32(dtype):
         cmp.composite_over(layers, [0], vp, out=other)
     with pytest.raises(ValueError, match="grad_out must hold float32"):
         cmp.composite_over_backward(layers, [0], vp, other)
+
+
+def test_workspaces_kept():
+    """A bounded number, the least recently used given back; grown on demand."""
+    first = cmp.workspace("kept", 100, "cpu")
+    assert first.numel() >= 100 and not bool(first.any())
+    assert cmp.workspace("kept", 50, "cpu") is first
+    for k in range(200):
+        cmp.workspace(f"kept {k}", 8, "cpu")
+        assert cmp.workspace("kept", 100, "cpu") is first
+    assert len(cmp._workspaces) <= 64
+    assert cmp.workspace("kept", 1000, "cpu").numel() >= 1000
+    cmp._workspaces.clear()

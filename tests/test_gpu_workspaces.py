@@ -1,0 +1,110 @@
+"""Workspaces of calls that are given none: one per stream, none shared with a
+captured call, and descriptors of their own for every backward pass."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1902_08755_amd as cmp
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda", 0)
+
+
+def test_workspace_per_stream():
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    here = cmp.workspace("test", 4096)
+    on_a = cmp.workspace("test", 4096, stream=a)
+    on_b = cmp.workspace("test", 4096, stream=b)
+    assert len({t.data_ptr() for t in (here, on_a, on_b)}) == 3
+    with torch.cuda.stream(a):
+        assert cmp.workspace("test", 4000) is on_a
+        grown = cmp.workspace("test", 9000)
+        assert grown is not on_a and grown.numel() >= 9000 and not bool(grown.any())
+        assert cmp.workspace("test", 4096, stream=b) is on_b
+    assert cmp.workspace("test", 4096) is here
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=a):
+        captured = cmp.workspace("test", 4096)
+    assert captured.data_ptr() not in {t.data_ptr() for t in (here, grown, on_b)}
+    assert cmp.workspace("test", 4096, stream=a) is grown
+    torch.cuda.synchronize()
+
+
+def _over_call(rng, n, W, H, dtype):
+    layers = []
+    for _ in range(n):
+        a = rng.random((H, W, 4)).astype(np.float32) * 0.5
+        layers.append(cmp.Image(torch.from_numpy(a).to(DEV, dtype), None, (0, 0, W, H)))
+    G = torch.from_numpy(rng.standard_normal((H, W, 4)).astype(np.float32)).to(DEV)
+    grads = [torch.zeros((H, W, 4), dtype=dtype, device=DEV) for _ in range(n)]
+    return layers, [int(v) for v in rng.permutation(n)], (0, 0, W, H), G, grads
+
+
+def test_calls_on_several_streams():
+    """Backward passes of more than 64 layers in both gradient types, and RL64
+    compressions, enqueued in turn on two streams."""
+    rng = np.random.default_rng(2)
+    calls = [_over_call(rng, 65 + 7 * k, 200, 150, (torch.float32, torch.float16)[k % 2])
+             for k in range(4)]
+    images = [[cmp.Image(torch.from_numpy(rng.integers(0, 3, (h, 700)).astype(np.int32)).to(DEV),
+                         None, (0, 0, 700, h))] for h in (300, 500)]
+    want = [[g.clone() for g in cmp.composite_over_backward(*c)] for c in calls]
+    coded = []
+    for im in images:
+        out, size, _ = cmp.rle64_compress(im)
+        coded.append(out[0][:int(size[0])].clone())
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    print("[gpu case] backward and RL64 on two streams", flush=True)
+    for _ in range(3):
+        for c in calls:
+            for g in c[4]:
+                g.zero_()
+        torch.cuda.synchronize()
+        got = [None] * len(images)
+        for k, c in enumerate(calls):
+            with torch.cuda.stream(streams[k % 2]):
+                cmp.composite_over_backward(*c)
+                if k < len(images):
+                    got[k] = cmp.rle64_compress(images[k])
+        torch.cuda.synchronize()
+        for c, w in zip(calls, want):
+            assert all(torch.equal(g, r) for g, r in zip(c[4], w))
+        for (out, size, status), ref in zip(got, coded):
+            assert not bool(status.any()) and int(size[0]) == ref.numel()
+            assert torch.equal(out[0][:ref.numel()], ref)
+
+
+def test_captured_calls_keep_their_workspace():
+    """Graphs that detect ROIs, compress and run a large backward pass without
+    workspaces given, replayed with eager calls on larger data in between."""
+    rng = np.random.default_rng(4)
+    call = _over_call(rng, 70, 150, 90, torch.float32)
+    d = torch.full((2, 300, 400), -1, dtype=torch.int32, device=DEV)
+    d[0, 20, 30] = d[1, 299, 399] = d[1, 100, 7] = 3
+    images = [cmp.Image(t, t, (0, 0, 400, 300)) for t in d]
+    big = torch.zeros((1500, 2000), dtype=torch.int32, device=DEV)
+    rois = cmp.roi_detect(images).clone()
+    want = [g.clone() for g in cmp.composite_over_backward(*call)]
+    out, size, _ = cmp.rle64_compress(images)
+    streams = [o[:int(s)].clone() for o, s in zip(out, size)]
+    got = torch.zeros((2, 4), dtype=torch.int32, device=DEV)
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    print("[gpu case] captured calls without workspaces", flush=True)
+    with torch.cuda.graph(g):
+        cmp.roi_detect(images, roi_out=got)
+        cmp.composite_over_backward(*call)
+        coded, sizes, status = cmp.rle64_compress(images)
+    for _ in range(4):
+        got.fill_(-5)
+        for t in call[4]:
+            t.zero_()
+        cmp.roi_detect([cmp.Image(big, None, (0, 0, 2000, 1500))] * 3)
+        cmp.rle64_compress([cmp.Image(big, None, (0, 0, 2000, 1500))])
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, rois) and not bool(status.any())
+        assert all(torch.equal(a, b) for a, b in zip(call[4], want))
+        for c, s, ref in zip(coded, sizes.tolist(), streams):
+            assert torch.equal(c[:s], ref)
