@@ -381,7 +381,6 @@ extern "C" cmp_status cmp_composite_over(const cmp_image* in, int32_t n, cmp_for
   CMP_REQUIRE(out_pitch >= viewport.w, "out_pitch < viewport.w");
   int tw = tile.w ? tile.w : 64, th = tile.h ? tile.h : 4;
   CMP_REQUIRE(tw > 0 && th > 0 && (int64_t)tw * th <= 65536, "bad tile %dx%d", tw, th);
-  over_tile_shape(tw, th);
   const bool tree = sched.kind == CMP_SCHED_BINARY_SWAP;
   if (tree && n > kOverPerPass) {
     set_error("binary-swap order supports at most %d layers", kOverPerPass);
@@ -391,9 +390,21 @@ extern "C" cmp_status cmp_composite_over(const cmp_image* in, int32_t n, cmp_for
   OverArgs a;
   memset(&a, 0, sizeof a);
   int64_t tiles = 0;
-  const int nreg = plan_regions(sched, viewport, tw, th, a.reg, &tiles);
+  int nreg = plan_regions(sched, viewport, tw, th, a.reg, &tiles);
   if (nreg < 0) return nreg;
-  CMP_REQUIRE(tiles < (1ll << 24), "too many tiles");
+  constexpr int64_t kTooMany = 1ll << 24;
+  CMP_REQUIRE(tiles < kTooMany, "too many tiles");
+  // The requested tile decides what is refused. The one it is run as can be
+  // more of them (16x16 over a view 16 pixels wide: four times as many); it is
+  // then made as much higher as the limit asks for, at most to the requested
+  // height, where it is never more.
+  const int rw = tw, rh = th;
+  over_tile_shape(tw, th);
+  if (tw != rw || th != rh) {
+    while ((nreg = plan_regions(sched, viewport, tw, th, a.reg, &tiles)) >= 0 && tiles >= kTooMany)
+      th = std::min(2 * th, rh);
+    if (nreg < 0) return nreg;
+  }
   a.out = out_rgba;
   a.out_pitch = out_pitch;
   a.vx = viewport.x;

@@ -1,8 +1,23 @@
 """Limits of the over entry points on the host: what is refused does not depend
-on a viewport that nothing reaches."""
+on the shape that a tile is run as, nor on a viewport that nothing reaches."""
 import ctypes
 
+import pytest
+
 import paper_1902_08755_amd as cmp
+
+SEQ = cmp.Schedule(0, 1)
+
+
+def _over(w, h, tile, sched=SEQ):
+    return cmp.lib().cmp_composite_over(None, 0, cmp.RGBA32F, None, cmp.Rect(0, 0, w, h), 0x10000,
+                                        w, sched, cmp.Tile(*tile), None)
+
+
+@pytest.mark.parametrize("w,h,tile,sched", [(5000, 5000, (1, 1), SEQ), (1 << 24, 1, (1, 1), SEQ),
+                                            (4096, 4096 * 8, (2, 2), cmp.Schedule(1, 7))])
+def test_too_many_tiles_are_refused(w, h, tile, sched):
+    assert _over(w, h, tile, sched) == cmp.CMP_EINVAL
 
 
 def test_no_layers_and_a_large_viewport():
