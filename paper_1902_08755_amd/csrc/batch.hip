@@ -217,8 +217,10 @@ struct TileShape {
 };
 static const TileShape kDepthTiles[] = {{64, 16}, {64, 32}, {64, 64}, {128, 16}, {128, 32},
                                         {256, 16}};
-static const TileShape kOverTiles[] = {{64, 4}, {128, 2}, {256, 1}, {32, 8}, {64, 8},
-                                       {16, 16}, {64, 16}, {128, 8}};
+// Widths are multiples of 64, so that every candidate is run as it stands
+// (over_tile_shape), and the defaults are among them.
+static const TileShape kOverTiles[] = {{64, 4}, {128, 2}, {256, 1}, {64, 8}, {128, 4},
+                                       {64, 16}, {128, 8}};
 // Without a tuned tile: over tiles of a wide view are single rows, whose
 // neighbours in the row share the fewest cache lines (256 jobs of 64 to 2048
 // pixels a side: 1600 us, with 128x4 for all of them 1680); in a narrow view
