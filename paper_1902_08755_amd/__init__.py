@@ -205,17 +205,16 @@ def _c_images(colors: Sequence, depths: Optional[Sequence], rois: Sequence, rgba
     n = len(colors)
     arr = (CImage * max(1, n))()
     flat, exact = [], True
-    for i, color in enumerate(colors):
-        roi = rois[i]
+    for i, (color, roi) in enumerate(zip(colors, rois)):
         shape = color.shape
         if 0 in shape:
             ptr, pitch = 0, int(roi[2])
         else:
             strides = color.stride()
             if rgba:
-                if len(shape) != 3 or shape[2] != 4 or strides[1:] != (4, 1) or strides[0] % 4:
+                if len(shape) != 3 or shape[2] != 4 or strides[1] != 4 or strides[2] != 1 or strides[0] % 4:
                     raise ValueError("expected a (h, pitch, 4) RGBA tensor")
-                if (dtype is not None and color.dtype != dtype
+                if (color.dtype is not dtype and dtype is not None
                         and int(roi[2]) > 0 and int(roi[3]) > 0):
                     raise ValueError(f"image {i}: expected {dtype} pixels, got {color.dtype}")
                 pitch = strides[0] // 4
@@ -227,18 +226,22 @@ def _c_images(colors: Sequence, depths: Optional[Sequence], rois: Sequence, rgba
                 raise ValueError("color must be a device tensor")
             ptr = color.data_ptr()
         dptr = 0
-        depth = depths[i] if depths is not None else None
-        if depth is not None and 0 not in (shape := depth.shape):
-            if not rgba:
-                strides = depth.stride()
-                if len(shape) != 2 or strides[1] != 1 or depth.element_size() != 4:
-                    raise ValueError(_U32_SHAPE)
-                if strides[0] != pitch:
-                    raise ValueError(f"image {i}: colour and depth pitches differ")
-            dptr = _cuda(depth, "depth")
-        flat += ptr, dptr, pitch
-        flat.extend(roi)
-        exact = exact and len(flat) == 7 * (i + 1)
+        if depths is not None:
+            depth = depths[i]
+            if depth is not None and 0 not in (shape := depth.shape):
+                if not rgba:
+                    strides = depth.stride()
+                    if len(shape) != 2 or strides[1] != 1 or depth.element_size() != 4:
+                        raise ValueError(_U32_SHAPE)
+                    if strides[0] != pitch:
+                        raise ValueError(f"image {i}: colour and depth pitches differ")
+                dptr = _cuda(depth, "depth")
+        try:
+            x, y, w, h = roi
+            flat += ptr, dptr, pitch, x, y, w, h
+        except ValueError:   # more or fewer numbers
+            flat += ptr, dptr, pitch, *roi
+            exact = False
     try:
         if not exact:
             raise struct.error
@@ -482,23 +485,30 @@ def workspace(tag: str, nbytes: int, device=None, stream=None) -> torch.Tensor:
     each stream has its own, allocated and filled in its order. A call that is
     captured gets one of its own, which the graph fills and keeps: the graph may
     run on any stream, beside other calls, after a cached one has been grown."""
-    with _on(stream):
-        dev = _dev() if device is None else torch.device(device)
-        handle = None
-        if dev.type == "cuda":
-            index = torch.cuda.current_device() if dev.index is None else dev.index
-            handle = torch._C._cuda_getCurrentRawStream(index)
-            if torch.cuda.is_current_stream_capturing():
-                return torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=dev)
-        key = (tag, dev, handle)
-        with _workspaces_lock:
-            ws = _workspaces.pop(key, None)
-            if ws is None or ws.numel() < nbytes:
-                ws = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=dev)
-            _workspaces[key] = ws
+    if stream is not None:
+        with _on(stream):
+            return workspace(tag, nbytes, device)
+    handle = None
+    if device is None:
+        index = torch.cuda.current_device()
+        dev = _cuda_device(index)
+    else:
+        dev = torch.device(device)
+        index = dev.index
+    if dev.type == "cuda":
+        handle = torch._C._cuda_getCurrentRawStream(
+            torch.cuda.current_device() if index is None else index)
+        if torch.cuda.is_current_stream_capturing():
+            return torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=dev)
+    key = (tag, dev, handle)
+    with _workspaces_lock:
+        ws = _workspaces.get(key)
+        if ws is None or ws.numel() < nbytes:
+            _workspaces[key] = ws = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=dev)
             if len(_workspaces) > _WORKSPACES_KEPT:
                 _workspaces.popitem(last=False)
-        return ws
+        _workspaces.move_to_end(key)
+    return ws
 
 
 def roi_detect(images: Sequence, fmt: int = RGBA8, roi_out=None, ws=None, stream=None):
