@@ -20,7 +20,10 @@
 // Items of 64 KB, 60 jobs: 109 us; 256 jobs of 64 to 2048 pixels a side, one
 // set of buffers: 1600 us (a single queue with items of 512 KB: 1841, of 128
 // KB: 1698; queues and items of 32 KB: 1638, of 128 KB: 1707; runs of 1, 16,
-// 64 items instead of 4: 1662, 1610, 1649). Completion counters let the last
+// 64 items instead of 4: 1662, 1610, 1649). Ten times as many items as of 512 KB
+// (175,000 of 8 bytes for 256 jobs) do not make preparation longer, since a
+// job's equal items are sorted as one: plan 0.8 -> 0.6 ms, upload of 1.6 MB in
+// place of 0.45 MB 0.24 -> 0.10 ms. Completion counters let the last
 // workgroup reset the queues, so a captured graph can replay the launch
 // without any reset node.
 //

@@ -16,9 +16,9 @@
 // three lane reads, the cover test and one load (the loop it replaces read
 // every placement from LDS and made it uniform once per pixel row and layer,
 // about 19 vector instructions each: the 256 jobs of the batch took 2155 us,
-// and 1880 with this, before the batch's queues were divided). Loads of up to over_batch layers are
-// issued before the first of them is blended; the blend chain itself stays
-// strictly in order.
+// and 1880 with this, before the batch's queues were divided). Loads of up to
+// over_batch layers are issued before the first of them is blended; the blend
+// chain itself stays strictly in order.
 #pragma once
 
 #include "cmp_internal.hpp"

@@ -70,9 +70,9 @@ struct RleCArgs {
 static_assert(sizeof(RleCArgs) <= 4096, "kernel arguments must fit in 4 KiB");
 
 // Workspace: the ticket counters (one per image, each on its own 128-byte
-// line, beside a count of finished workgroups), control words (the call epoch on one line; the count of finished
-// workgroups and the most flags any call has used on another), then the
-// look-back flags. It is zero-filled once, before its first use; every call
+// line, beside a count of finished workgroups), control words (the call epoch
+// on one line; the count of finished workgroups and the most flags any call
+// has used on another), then the look-back flags. It is zero-filled once, before its first use; every call
 // leaves it ready for the next: the last workgroup to finish zeroes the
 // tickets and the count and advances the epoch, and a flag written by an
 // earlier call (another epoch) reads as not ready, so the flags are not

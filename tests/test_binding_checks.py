@@ -54,7 +54,8 @@ def test_layers_of_several_types(first, other):
         cmp.OverComposite.apply(order, vp, rois, *pixels)
     # a layer that covers nothing is not read: refused for its device only
     with pytest.raises(ValueError, match="device tensor"):
-        cmp.composite_over([layers[0], cmp.Image(pixels[1], None, (0, 0, 0, 0))], order, vp, out=out)
+        cmp.composite_over([layers[0], cmp.Image(pixels[1], None, (0, 0, 0, 0))], order, vp,
+                           out=out)
 
 
 @pytest.mark.parametrize("fmt,dtype", [(cmp.RGBA32F, torch.float16), (cmp.RGBA32F, torch.int16),

@@ -41,7 +41,8 @@ def _workgroups():
     return workgroups
 
 
-@pytest.mark.parametrize("case", ["one more", "33 more", "costly over", "costly depth", "two costly"])
+@pytest.mark.parametrize("case", ["one more", "33 more", "costly over", "costly depth",
+                                  "two costly"])
 def test_batch_draws(case):
     rng = np.random.default_rng(len(case))
     if case.endswith("more"):   # jobs of one tile each

@@ -66,6 +66,7 @@ def test_roi_workspace_of_the_coarse_bands():
             roi = cmp.roi_detect(imgs, ws=ws)
             torch.cuda.synchronize()
             assert [tuple(r) for r in roi.cpu().tolist()] == refs
+    ws = torch.zeros(TICKETS + 16 * (coarse - 1), dtype=torch.uint8, device=DEV)
     with pytest.raises(cmp.CmpError) as e:   # refused on the host
-        cmp.roi_detect(imgs, ws=torch.zeros(TICKETS + 16 * (coarse - 1), dtype=torch.uint8, device=DEV))
+        cmp.roi_detect(imgs, ws=ws)
     assert e.value.status == cmp.CMP_ENOSPC

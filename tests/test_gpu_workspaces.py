@@ -1,5 +1,7 @@
 """Workspaces of calls that are given none: one per stream, none shared with a
 captured call, and descriptors of their own for every backward pass."""
+import types
+
 import numpy as np
 import pytest
 import torch
@@ -22,6 +24,8 @@ def test_workspace_per_stream():
         assert grown is not on_a and grown.numel() >= 9000 and not bool(grown.any())
         assert cmp.workspace("test", 4096, stream=b) is on_b
     assert cmp.workspace("test", 4096) is here
+    handle = types.SimpleNamespace(cuda_stream=b.cuda_stream)   # all that a call asks of a stream
+    assert cmp.workspace("test", 4096, stream=handle) is on_b
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g, stream=a):
         captured = cmp.workspace("test", 4096)
